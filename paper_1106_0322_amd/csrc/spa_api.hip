@@ -1166,8 +1166,10 @@ extern "C" spa_status spa_smc_init(const spa_smc_config *cfg, const uint8_t *X_h
     return fail(SPA_ERR_HIP);
   }
   launch_col_stats(h->dX, h->dy, n, p, h->mu, h->s, h->inv_s, h->ytil, h->dbad, h->stream);
-  if (!h->f8_terms && (st = tiled_sampler(h) ? ensure_xpack(h, h->prec) : ensure_spack(h, h->prec)) != SPA_OK)
-    return fail(st);
+  // the handle's own precision is always prepared, for its sweeps and for spa_smc_loglik_noalloc
+  // (FP32 MALA: the tiled copy for the one, the streamed copy for the other)
+  if (!h->f8_terms && tiled_sampler(h) && (st = ensure_xpack(h, h->prec)) != SPA_OK) return fail(st);
+  if (streamed(h->prec) && (st = ensure_spack(h, h->prec)) != SPA_OK) return fail(st);
   if (h->move == SPA_MOVE_SINGLE) {
     h->ss_rows = single_site_rows(n);   // n <= single_site_max_n() was checked above
     if ((st = dalloc(h, &h->xs_ss, h->psz * (size_t)p * h->ss_rows)) != SPA_OK) return fail(st);
@@ -1373,6 +1375,8 @@ extern "C" spa_status spa_smc_step(spa_smc *h, spa_smc_stats *out) {
 static spa_status prep_operand(spa_smc *h, const void *beta, int M, int is_f64, Prec prec) {
   spa_status st;
   if ((st = ensure_xpack(h, prec)) != SPA_OK) return st;
+  // an FP32 gradient also prepares the copy of spa_smc_loglik_noalloc
+  if (streamed(prec) && (st = ensure_spack(h, prec)) != SPA_OK) return st;
   const int PP = h->xp[static_cast<int>(prec)].PP;
   const int Mpad = round_up(M, kPartPad);
   OpScratch &o = h->scr[static_cast<int>(prec)];

@@ -92,3 +92,36 @@ def test_noalloc_refusals():
     torch.cuda.synchronize()
     assert np.allclose(out[:64].cpu().numpy(), s.loglik(small, "fp32").cpu().numpy(), rtol=0, atol=0)
     s.close()
+
+
+@pytest.mark.parametrize("move,prec", [("mala", "fp32"), ("mala", "fp64"), ("mala", "bf16x2"), ("single", "fp32")])
+def test_noalloc_own_precision_is_always_prepared(move, prec):
+    """A fresh handle of any move serves its own precision, without a loglik call before."""
+    import torch
+    from paper_1106_0322_amd import SamplerConfig, SpaSMC
+    cfg, X, y, Xs = dataset("n500_p10_rwm_fp64")
+    s = SpaSMC(SamplerConfig(n=X.shape[0], p=X.shape[1], N=64, a=cfg.a, lambdas=np.geomspace(10, 1, 2), move=move,
+                             sweeps=0, init_sweeps=0, prec=prec, seed=0), X, y)
+    b = torch.from_numpy(particles(33, X.shape[1], seed=5)).to("cuda", torch.float64 if prec == "fp64" else torch.float32)
+    out = torch.empty(33, dtype=torch.float64, device="cuda")
+    print(f"noalloc of a fresh {move} {prec} handle", flush=True)
+    s.loglik_noalloc(b, out, prec)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), s.loglik(b, prec).cpu().numpy())
+    s.close()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "bf16x2"])
+def test_noalloc_after_a_gradient_call(prec):
+    """spa_smc_grad prepares its precision for spa_smc_loglik_noalloc too."""
+    import torch
+    own = "bf16x2" if prec != "bf16x2" else "fp32"
+    s, X, y, Xs = _handle("n500_p10_rwm_fp64", own)
+    b = torch.from_numpy(particles(40, X.shape[1], seed=6)).to("cuda", torch.float32)
+    s.grad(b, 0.3, prec)
+    out = torch.empty(40, dtype=torch.float64, device="cuda")
+    print(f"noalloc after grad {prec}", flush=True)
+    s.loglik_noalloc(b, out, prec)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), s.loglik(b, prec).cpu().numpy())
+    s.close()
