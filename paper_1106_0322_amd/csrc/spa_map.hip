@@ -6,19 +6,18 @@
 // beta_j <- S(beta_j + 4 g_j / n, 4 w_j / n), g_j = sum_k (y_k - sigma(eta_k)) X_std,kj.
 //
 // One workgroup of one to eight wave64s per start point.  Thread t of T holds individuals t,
-// t+T, ...  With the sign s_k = +1 for a case and -1 for a control, the residual is
-// u_k = y_k - sigma(eta_k) = s_k / (1 + E_k), E_k = exp(s_k eta_k); the thread keeps E_k and
-// u_k of its individuals in registers (E = +inf in padded ones: u = 2^-1000).  A column of
-// standardised genotypes is x = (c - mu_j)/s_j, c = 0, 1, 2, so
+// t+T, ...: E_k = exp(-eta_k) and the residual u_k = y_k - sigma(eta_k) = y_k - 1 / (1 + E_k) in
+// registers (E = +inf and y = 0 in padded ones: u = -2^-1000; an E that is not a number counts as
+// sigma = 0).  A column of standardised genotypes is x = (c - mu_j)/s_j, c = 0, 1, 2, so
 //   g_j = (sum_k c_kj u_k - mu_j R) / s_j,   R = sum_k u_k,
 // and the sum over c is taken as 4 sum_k w_kj u_k - 2 R with w = 1/2 + c/4, whose FP64 bits are
 // the genotype's two bits shifted into a constant high word: two integer instructions and one
 // FMA per individual and column, no table (the standardised values read from LDS, 8 bytes per
 // individual and column, were the longest part of a sweep over zero coefficients).  A move
-// beta_j += delta multiplies every E_k by one of six constants exp(delta s x_c): lanes 0..7 of
-// each wave put them in a table in LDS, then per individual one table read, one multiply and
-// a reciprocal (hardware estimate refined by one Newton step).  A thread's genotypes of a
-// column are two-bit fields of one word (two above 16 individuals): one load per thread and
+// beta_j += delta multiplies every E_k by one of three constants exp(-delta x_c): lanes 0..3 of
+// each wave put them in a table in LDS (1 for padded individuals), then per individual one table
+// read, one multiply and a reciprocal (hardware estimate refined by one Newton step).  A thread's
+// genotypes of a column are two-bit fields of one word (two above 16 individuals): one load per thread and
 // column.  As in the oracle, eta is recomputed from the coefficients at the start of every
 // coordinate sweep, which also bounds the rounding of the products to one sweep; zero
 // coefficients add nothing and are passed over.
@@ -89,10 +88,10 @@ inline int map_rows(int n_pad) {
   return R <= 2 ? 2 : R <= 4 ? 4 : R <= 6 ? 6 : R <= 8 ? 8 : R <= 10 ? 10 : R <= 12 ? 12 : R <= 16 ? 16 : 20;
 }
 
-// 1 / (1 + e) for e >= 0 (e = +inf gives 2^-1000): hardware reciprocal (relative error near
+// 1 / (1 + e) for e >= 0 (2^-1000 for +inf and for NaN): hardware reciprocal (relative error near
 // 2^-23) and one Newton step (error near 2^-46, squared by the step).
 __device__ __forceinline__ double inv1p(double e) {
-  const double d = fmin(1.0 + e, 0x1p1000);   // e = +inf: 2^-1000
+  const double d = fmin(1.0 + e, 0x1p1000);
   double r = __builtin_amdgcn_rcp(d);
   const double q = fma(-d, r, 1.0);
   return fma(r, q, r);
@@ -167,7 +166,7 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
   __shared__ double bl[kMapMaxP], tl[kMapMaxP], gl[kMapMaxP], pl[kMapMaxP], mul[kMapMaxP], isl[kMapMaxP];
   __shared__ __align__(16) double part[2][NW][8];
   __shared__ double red[NW];
-  __shared__ double cltab[NW][8];          // per wave: exp(delta s x_c), index c + 4 for s = +1
+  __shared__ double cltab[NW][4];          // per wave: exp(-delta x_c), 1 for code 3
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int s = blockIdx.x;                      // start point
   const int n = a.n, p = a.p;
@@ -183,11 +182,11 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
     mul[j] = a.mu[j];
     isl[j] = a.inv_s[j];
   }
-  uint32_t cases = 0;                            // bit r: individual tid + NT r is a case
+  double yk[R];                                  // labels of individuals tid + NT r, 0 in padded ones
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int k = tid + NT * r;
-    if (k < n && a.y[k]) cases |= 1u << r;
+    yk[r] = k < n && a.y[k] ? 1.0 : 0.0;
   }
   // one column's words of this wave's threads -> a slot
   auto fill = [&](const int c, const int slot) {
@@ -202,13 +201,7 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
   }
   __syncthreads();
   double E[R], u[R] = {};
-  // E is in place: the residual with its sign
-  auto residual = [&](const int r) {
-    const double iv = inv1p(E[r]);
-    const uint32_t neg = (~(cases >> r) & 1u) << 31;
-    u[r] = __hiloint2double(__double2hiint(iv) ^ static_cast<int>(neg), __double2loint(iv));
-  };
-  // s_k eta_k from the coefficients (the sweep's fresh linear predictor), non-zero columns only,
+  // eta_k from the coefficients (the sweep's fresh linear predictor), non-zero columns only,
   // four columns' words in flight: with w = 1/2 + c/4, b (c - mu) / s = (4 b / s) w - b (2 + mu) / s
   auto predictor = [&](double (&eta)[R]) {
     constexpr int B = 4;
@@ -267,27 +260,20 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
     }
     cst = wave_total_f64(cst);                   // every block of columns has been visited
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const double e = eta[r] + cst;
-      eta[r] = (cases >> r) & 1u ? e : -e;
-    }
+    for (int r = 0; r < R; ++r) eta[r] += cst;
   };
 
   // a coefficient moves by delta (uniform)
   auto move = [&](const double delta, const double dmu, const double dis, const uint32_t (&wd)[WN]) {
-    // lanes 0..7 put the genotypes' factors in the wave's table (code 3, padded: 1); a wave's
+    // lanes 0..3 put the genotypes' factors in the wave's table (code 3, padded: 1); a wave's
     // LDS accesses are processed in order, and the wave barrier keeps the compiler from
     // moving the table reads above the write
-    if (lane < 8) {
-      const int code = lane & 3;
-      const double x = (static_cast<double>(code) - dmu) * dis;
-      cltab[wave][lane] = code == 3 ? 1.0 : exp(delta * (lane < 4 ? -x : x));
-    }
+    if (lane < 4) cltab[wave][lane] = lane == 3 ? 1.0 : exp(-delta * ((static_cast<double>(lane) - dmu) * dis));
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      E[r] *= cltab[wave][code_at<R>(wd, r) + 4 * ((cases >> r) & 1u)];
-      residual(r);
+      E[r] *= cltab[wave][code_at<R>(wd, r)];
+      u[r] = yk[r] - inv1p(E[r]);
     }
   };
   int parity = 0, tag = -1;                      // tag: the block whose column this lane's slot holds
@@ -306,8 +292,8 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
           const double old = u[r];
-          E[r] = tid + NT * r < n ? exp(eta[r]) : INFINITY;
-          residual(r);
+          E[r] = tid + NT * r < n ? exp(-eta[r]) : INFINITY;
+          u[r] = yk[r] - inv1p(E[r]);
           drift += fabs(u[r] - old);
         }
         // by how much the products' residuals were off counts as path: |4 dg_j / n| <= 4 sum |du|
@@ -492,14 +478,14 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
     }
   }
   __syncthreads();
-  // log posterior at the mode: sum_k -log(1 + exp(-s_k eta_k)) + sum_j log Gt(beta_j)
+  // log posterior at the mode: sum_k [y eta - softplus(eta)] + sum_j log Gt(beta_j)
   double eta[R];
   predictor(eta);
   double acc = 0.0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int k = tid + NT * r;
-    if (k < n) acc += fmin(eta[r], 0.0) - log1p(exp(-fabs(eta[r])));
+    if (k < n) acc += yk[r] * eta[r] - (fmax(eta[r], 0.0) + log1p(exp(-fabs(eta[r]))));
   }
   for (int j = tid; j < p; j += NT) acc += gt_logpdf(bl[j], pr);
   acc = wave_sum(acc);
