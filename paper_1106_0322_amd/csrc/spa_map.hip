@@ -9,16 +9,19 @@
 // t+T, ...: E_k = exp(-eta_k) and the residual u_k = y_k - sigma(eta_k) = y_k - 1 / (1 + E_k) in
 // registers (E = +inf and y = 0 in padded ones: u = -2^-1000; an E that is not a number counts as
 // sigma = 0).  A column of standardised genotypes is x = (c - mu_j)/s_j, c = 0, 1, 2, so
-//   g_j = (sum_k c_kj u_k - mu_j R) / s_j,   R = sum_k u_k,
-// and the sum over c is taken as 4 sum_k w_kj u_k - 2 R with w = 1/2 + c/4, whose FP64 bits are
-// the genotype's two bits shifted into a constant high word: two integer instructions and one
-// FMA per individual and column, no table (the standardised values read from LDS, 8 bytes per
-// individual and column, were the longest part of a sweep over zero coefficients).  A move
+//   g_j = (sum_k (c_kj - mu_j) u_k) / s_j,
+// with c - mu formed per individual by one FMA: the genotype's two bits shifted to the exponent's
+// lowest bits are the double c 2^-1022, so that a column costs two integer instructions and two
+// FMAs per individual, no table (the standardised values read from LDS, 8 bytes per individual
+// and column, were the longest part of a sweep over zero coefficients).  Subtracting mu from the
+// sums instead, sum c u - mu sum u, would save one FMA but cancels where sum u is large (unbalanced
+// labels), and 1 / s_j enlarges what is left (rare markers): errors of the mode 1e-14 against
+// 1e-16 at 90 % cases and an allele frequency of 0.0005.  A move
 // beta_j += delta multiplies every E_k by one of three constants exp(-delta x_c): lanes 0..3 of
 // each wave put them in a table in LDS (1 for padded individuals), then per individual one table
 // read, one multiply and a reciprocal (hardware estimate refined by one Newton step).  A thread's
-// genotypes of a column are two-bit fields of one word (two above 16 individuals): one load per thread and
-// column.  As in the oracle, eta is recomputed from the coefficients at the start of every
+// genotypes of a column are two-bit fields of one word (two above 16 individuals): one load per
+// thread and column.  As in the oracle, eta is recomputed from the coefficients at the start of every
 // coordinate sweep, which also bounds the rounding of the products to one sweep; zero
 // coefficients add nothing and are passed over.
 //
@@ -33,9 +36,9 @@
 // small and nearly all zero coefficients are decided so.
 //
 // Runs of columns.  An update that leaves beta_j as it was does not change u, so the gradients
-// of the columns after it are those of the same u.  Of the columns that need a look, one,
-// three or seven (by how many zero coefficients come first: a coefficient that is zero usually
-// stays so) are reduced together with R: one barrier and one reduction latency for the run.
+// of the columns after it are those of the same u.  Of the columns that need a look, one, two,
+// four or eight (by how many zero coefficients come first: a coefficient that is zero usually
+// stays so) are reduced together: one barrier and one reduction latency for the run.
 // The reduction of 2, 4 or 8 values over a wave halves the number of values at each of its
 // first steps; after the barrier the lane that holds a column's coefficient decides it, and a
 // ballot finds the first that moves.  The columns before it are done, the gradients after it
@@ -97,12 +100,12 @@ __device__ __forceinline__ double inv1p(double e) {
   return fma(r, q, r);
 }
 
-// 1/2 + c/4 for the genotype of a thread's r-th individual (2 bits each), and the genotype.
+// c - mu for the genotype c of a thread's r-th individual (2 bits each), rounded once; and c.
 template <int R>
-__device__ __forceinline__ double weight_at(const uint32_t (&w)[map_words(R)], int r) {
+__device__ __forceinline__ double centred_at(const uint32_t (&w)[map_words(R)], int r, double mu) {
   const int at = 2 * (r % 16);
-  const uint32_t f = at <= 19 ? w[r / 16] << (19 - at) : w[r / 16] >> (at - 19);
-  return __hiloint2double(static_cast<int>((f & 0x180000u) | 0x3FE00000u), 0);
+  const uint32_t f = at <= 20 ? w[r / 16] << (20 - at) : w[r / 16] >> (at - 20);
+  return fma(__hiloint2double(static_cast<int>(f & 0x300000u), 0), 0x1p1022, -mu);   // c 2^-1022
 }
 template <int R>
 __device__ __forceinline__ int code_at(const uint32_t (&w)[map_words(R)], int r) {
@@ -202,27 +205,28 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
   __syncthreads();
   double E[R], u[R] = {};
   // eta_k from the coefficients (the sweep's fresh linear predictor), non-zero columns only,
-  // four columns' words in flight: with w = 1/2 + c/4, b (c - mu) / s = (4 b / s) w - b (2 + mu) / s
+  // four columns' words in flight
   auto predictor = [&](double (&eta)[R]) {
     constexpr int B = 4;
-    double cst = 0.0, b4l = 0.0;                 // lanes: the constants, and 4 b / s of 64 columns
+    double bsl = 0.0, mul64 = 0.0;               // lanes: b / s and mu of 64 columns
 #pragma unroll
     for (int r = 0; r < R; ++r) eta[r] = 0.0;
     int base = -64;
     unsigned long long left = 0;
-    auto next = [&](double &b4) -> int {         // the next non-zero column, or -1 (uniform)
+    auto next = [&](double &bs, double &m) -> int {   // the next non-zero column, or -1 (uniform)
       while (left == 0) {
         base += 64;
         if (base >= p) return -1;
         const int j = min(base + lane, p - 1);
-        const double bj = base + lane < p ? bl[j] : 0.0, bs = bj * isl[j];
-        b4l = 4.0 * bs;
-        cst -= bs * (2.0 + mul[j]);
+        const double bj = base + lane < p ? bl[j] : 0.0;
+        bsl = bj * isl[j];
+        mul64 = mul[j];
         left = __ballot(bj != 0.0);
       }
       const int l = __builtin_ctzll(left);
       left &= left - 1;
-      b4 = read_lane_f64(b4l, l);
+      bs = read_lane_f64(bsl, l);
+      m = read_lane_f64(mul64, l);
       return base + l;
     };
     auto load = [&](const int c, uint32_t (&w)[WN]) {
@@ -231,36 +235,34 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
       for (int q = 0; q < WN; ++q) w[q] = col[q * NT];
     };
     int c[B], cn[B];
-    double b4[B], bn[B];
+    double bs[B], bn[B], m[B], mn[B];
     uint32_t w[B][WN], wn[B][WN];
 #pragma unroll
     for (int q = 0; q < B; ++q) {
-      c[q] = next(b4[q]);
+      c[q] = next(bs[q], m[q]);
       load(c[q], w[q]);
     }
     while (c[0] >= 0) {
 #pragma unroll
       for (int q = 0; q < B; ++q) {
-        cn[q] = next(bn[q]);
+        cn[q] = next(bn[q], mn[q]);
         load(cn[q], wn[q]);
       }
 #pragma unroll
       for (int q = 0; q < B; ++q) {
         if (c[q] < 0) continue;                  // uniform
 #pragma unroll
-        for (int r = 0; r < R; ++r) eta[r] = fma(b4[q], weight_at<R>(w[q], r), eta[r]);
+        for (int r = 0; r < R; ++r) eta[r] = fma(bs[q], centred_at<R>(w[q], r, m[q]), eta[r]);
       }
 #pragma unroll
       for (int q = 0; q < B; ++q) {
         c[q] = cn[q];
-        b4[q] = bn[q];
+        bs[q] = bn[q];
+        m[q] = mn[q];
 #pragma unroll
         for (int k = 0; k < WN; ++k) w[q][k] = wn[q][k];
       }
     }
-    cst = wave_total_f64(cst);                   // every block of columns has been visited
-#pragma unroll
-    for (int r = 0; r < R; ++r) eta[r] += cst;
   };
 
   // a coefficient moves by delta (uniform)
@@ -355,10 +357,10 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
                 for (int k = 0; k < WN; ++k) w0[k] = slots[((slot0 + f + 1) * WN + k) * NT + tid];
               }
               const double fmu = read_lane_f64(mu, f), fis = read_lane_f64(is, f), fthr = read_lane_f64(thr, f);
-              const double fb = read_lane_f64(b, f), c0m = -(2.0 + fmu);
+              const double fb = read_lane_f64(b, f);
               double g = 0.0;
 #pragma unroll
-              for (int r = 0; r < R; ++r) g = fma(fma(4.0, weight_at<R>(w, r), c0m), u[r], g);
+              for (int r = 0; r < R; ++r) g = fma(centred_at<R>(w, r, fmu), u[r], g);
               double t;
               if constexpr (NW == 1) {
                 t = wave_total_f64(g);
@@ -396,29 +398,29 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
           }
           const int zeros = __popcll(nzc ? cand & ((nzc & (0ull - nzc)) - 1) : cand);
           const int rank = __popcll(cand & ((1ull << lane) - 1));   // a candidate's place
-          double t = 0.0, Rs = 0.0;
+          double t = 0.0;
           auto sums = [&](auto v_c) {
             constexpr int V = decltype(v_c)::value;
-            uint32_t w[V - 1][WN];
-            unsigned long long m = cand;
+            uint32_t w[V][WN];
+            double m[V], g[V];
+            unsigned long long c = cand;
 #pragma unroll
-            for (int q = 0; q < V - 1; ++q) {    // absent candidates repeat the last one, unused
-              const int l = __builtin_ctzll(m);
-              if (m & (m - 1)) m &= m - 1;
+            for (int q = 0; q < V; ++q) {        // absent candidates repeat the last one, unused
+              const int l = __builtin_ctzll(c);
+              if (c & (c - 1)) c &= c - 1;
+              m[q] = read_lane_f64(mu, l);
+              g[q] = 0.0;
 #pragma unroll
               for (int k = 0; k < WN; ++k) w[q][k] = q == 0 ? w0[k] : slots[((slot0 + l) * WN + k) * NT + tid];
             }
-            double g[V];
 #pragma unroll
-            for (int q = 0; q < V; ++q) g[q] = 0.0;
+            for (int r = 0; r < R; ++r)
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-              g[0] += u[r];
-#pragma unroll
-              for (int q = 1; q < V; ++q) g[q] = fma(weight_at<R>(w[q - 1], r), u[r], g[q]);
-            }
-            const double x = wave_sums<V>(g, label);
-            const int want = min(rank + 1, V - 1);   // the value this lane's column takes
+              for (int q = 0; q < V; ++q) g[q] = fma(centred_at<R>(w[q], r, m[q]), u[r], g[q]);
+            const int want = min(rank, V - 1);   // the value this lane's column takes
+            double x;
+            if constexpr (V == 1) x = wave_total_f64(g[0]);
+            else x = wave_sums<V>(g, label);
             if constexpr (NW > 1) {
               if (lane < 8 && label < V) part[parity][wave][label] = x;
               __syncthreads();
@@ -427,26 +429,25 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
               z += dpp_move_f64<0xB1>(z);                             // partner k ^ 1
               if constexpr (NW >= 4) z += dpp_move_f64<0x4E>(z);      // k ^ 2
               if constexpr (NW == 8) z += dpp_move_f64<0x141>(z);     // 7 - k
-              Rs = read_lane_f64(z, 0);
-              if constexpr (V == 2) t = read_lane_f64(z, 8);
-              else t = __shfl(z, 8 * want, kWave);
+              t = V == 1 ? read_lane_f64(z, 0) : __shfl(z, 8 * want, kWave);
               parity ^= 1;
             } else {
               // from the lane of lanes 0..7 that holds the value
               const int x2 = (want >> 2) & 1;
-              t = __shfl(x, ((want ^ (x2 ? 3 : 0)) & 3) | x2 << 2, kWave);
-              Rs = read_lane_f64(x, 0);
+              t = V == 1 ? x : __shfl(x, ((want ^ (x2 ? 3 : 0)) & 3) | x2 << 2, kWave);
             }
           };
-          const int V = zeros == 0 ? 2 : zeros <= 2 ? 4 : 8;
-          if (V == 2)
-            sums(std::integral_constant<int, 2>{});
+          const int V = zeros == 0 ? 1 : zeros == 1 ? 2 : zeros <= 3 ? 4 : 8;
+          if (V == 8)
+            sums(std::integral_constant<int, 8>{});
           else if (V == 4)
             sums(std::integral_constant<int, 4>{});
+          else if (V == 2 || R <= 12)            // (up to 12: a zero coefficient comes first)
+            sums(std::integral_constant<int, 2>{});
           else
-            sums(std::integral_constant<int, 8>{});
-          const bool mine = look && rank < V - 1;
-          const double gs = inv_n4 * (((4.0 * t - 2.0 * Rs) - mu * Rs) * is), z = b + gs;
+            sums(std::integral_constant<int, 1>{});
+          const bool mine = look && rank < V;
+          const double gs = inv_n4 * (t * is), z = b + gs;
           const double nb = z > thr ? z - thr : (z < -thr ? z + thr : 0.0);
           const double d = nb - b;
           const unsigned long long moved = __ballot(mine && d != 0.0), decided = __ballot(mine);

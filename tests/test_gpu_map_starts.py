@@ -25,14 +25,15 @@ def _map_em(Xs, y, b0, a, lam, outer, inner):
                 for j in range(p):
                     z = b[j] + 4.0 / n * ((y - np.where(np.isnan(eta), 0.0, expit(eta))) @ Xs[:, j])
                     nb = z - thr[j] if z > thr[j] else z + thr[j] if z < -thr[j] else 0.0
-                    if nb != b[j]:
-                        eta = eta + (nb - b[j]) * Xs[:, j]
+                    delta = nb - b[j]             # not a number for an infinite coefficient: it moves
+                    if delta != 0.0:
+                        eta = eta + delta * Xs[:, j]
                     b[j] = nb
         modes.append(b)
     return np.stack(modes)
 
 
-@pytest.mark.parametrize("value", [np.nan], ids=["nan"])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf], ids=["nan", "inf", "minus_inf"])
 @pytest.mark.parametrize("n,p", [(100, 9), (700, 20), (6100, 12), (8300, 7)])
 def test_map_em_from_non_finite_starts(n, p, value):
     import torch
