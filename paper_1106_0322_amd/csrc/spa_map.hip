@@ -54,14 +54,15 @@
 // the ones that are asked for, sweep after sweep).
 //
 // What bounds it: a chain of coordinate updates, each a reduction and a barrier; the start
-// points' workgroups are all the parallelism there is.  Two starts, against one update per
-// barrier in 512 threads with the standardised values in a table:
-//   n = 5000, p = 200, 50 x 5 sweeps: 42 of 400 coefficients non-zero 52.8 -> 14 ms, 324 73.3 ->
-//   70.3, all 79.6 -> 81.9; n = 10000, p = 100, 20 x 3: 16.1 -> 5.9; n = 500, p = 50, 30 x 5: 4 of 100
-//   non-zero 3.65 -> 0.61, 54 4.52 -> 3.95, all 5.2 -> 5.7; n = 120, p = 50, 30 x 3: 2.16 -> 0.15 ms.
-// With every coefficient non-zero nothing is passed over and an update issues about as much
-// as before (3 % more at n = 5000, 9 % at n = 500, less at n = 10000 and n = 100); along a path of
-// scales those are the few largest.
+// points' workgroups are all the parallelism there is.  Two starts, 10 x 5 sweeps, against one
+// update per barrier in 512 threads with the standardised values in a table (ms):
+//   n = 5000, p = 200: 13 of 400 coefficients non-zero 10.66 -> 3.07, 368 15.3 -> 14.1, all
+//   15.4 -> 14.3; n = 10000, p = 100: 18 of 200 12.8 -> 3.0, all 16.5 -> 12.4; n = 1000, p = 100:
+//   1 of 200 2.94 -> 0.47, all 3.91 -> 3.66; n = 500, p = 50: none 1.22 -> 0.14, 66 of 100 1.58 ->
+//   1.25, all 1.72 -> 1.58; n = 120, p = 50: none 1.21 -> 0.085, all 1.72 -> 1.24.
+// With every coefficient non-zero nothing is passed over: what counts is the latency of an
+// update, that is the table reads and the chains of E and u side by side (see move) and the
+// predictor's loads ahead of their use.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -82,19 +83,20 @@ constexpr int kMapMaxThreads = 512;
 constexpr int map_words(int R) { return R <= 16 ? 1 : 2; }
 // Threads of a start point's workgroup and individuals per thread.  Fewer waves make the
 // reduction and the barrier of an update cheaper, fewer individuals per thread its vector
-// work: four per thread up to the eight waves that two per SIMD allow (n = 500, p = 50, 150
-// sweeps, every coefficient non-zero: 6.1 ms in 64 threads of 8, 5.7 ms in 128 of 4, 6.5 ms in
-// 256 of 2; sparse, 90 sweeps: 0.35, 0.30, 0.29 ms).
-inline int map_threads(int n_pad) { return n_pad <= 256 ? 64 : n_pad <= 512 ? 128 : n_pad <= 1024 ? 256 : 512; }
+// work: one wave up to four per thread, then one per SIMD, then two (n = 500, p = 50, 50
+// sweeps from two starts: every coefficient non-zero 1.75 ms in 128 threads of 4, 1.57 ms in 256
+// of 2; none 0.118 and 0.102 ms).
+inline int map_threads(int n_pad) { return n_pad <= 256 ? 64 : n_pad <= 1024 ? 256 : 512; }
 inline int map_rows(int n_pad) {
   const int t = map_threads(n_pad), R = (n_pad + t - 1) / t;
-  return R <= 2 ? 2 : R <= 4 ? 4 : R <= 6 ? 6 : R <= 8 ? 8 : R <= 10 ? 10 : R <= 12 ? 12 : R <= 16 ? 16 : 20;
+  return R <= 1 ? 1 : R <= 2 ? 2 : R <= 4 ? 4 : R <= 6 ? 6 : R <= 8 ? 8 : R <= 10 ? 10 : R <= 12 ? 12 : R <= 16 ? 16 : 20;
 }
 
-// 1 / (1 + e) for e >= 0 (2^-1000 for +inf and for NaN): hardware reciprocal (relative error near
-// 2^-23) and one Newton step (error near 2^-46, squared by the step).
+// 1 / (1 + e) for e >= 0 (2^-1000 for +inf and for NaN): hardware reciprocal of inv1p_arg (relative
+// error near 2^-23) and one Newton step (error near 2^-46, squared by the step).
+__device__ __forceinline__ double inv1p_arg(double e) { return fmin(1.0 + e, 0x1p1000); }
 __device__ __forceinline__ double inv1p(double e) {
-  const double d = fmin(1.0 + e, 0x1p1000);
+  const double d = inv1p_arg(e);
   double r = __builtin_amdgcn_rcp(d);
   const double q = fma(-d, r, 1.0);
   return fma(r, q, r);
@@ -204,8 +206,8 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
   }
   __syncthreads();
   double E[R], u[R] = {};
-  // eta_k from the coefficients (the sweep's fresh linear predictor), non-zero columns only,
-  // four columns' words in flight
+  // eta_k from the coefficients (the sweep's fresh linear predictor), non-zero columns only, in
+  // groups of up to four of a block of 64, the next group's words in flight
   auto predictor = [&](double (&eta)[R]) {
     constexpr int B = 4;
     double bsl = 0.0, mul64 = 0.0;               // lanes: b / s and mu of 64 columns
@@ -213,50 +215,41 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
     for (int r = 0; r < R; ++r) eta[r] = 0.0;
     int base = -64;
     unsigned long long left = 0;
-    auto next = [&](double &bs, double &m) -> int {   // the next non-zero column, or -1 (uniform)
+    auto group = [&](double (&bs)[B], double (&m)[B], uint32_t (&w)[B][WN]) -> bool {
       while (left == 0) {
         base += 64;
-        if (base >= p) return -1;
+        if (base >= p) return false;
         const int j = min(base + lane, p - 1);
         const double bj = base + lane < p ? bl[j] : 0.0;
         bsl = bj * isl[j];
         mul64 = mul[j];
         left = __ballot(bj != 0.0);
       }
-      const int l = __builtin_ctzll(left);
-      left &= left - 1;
-      bs = read_lane_f64(bsl, l);
-      m = read_lane_f64(mul64, l);
-      return base + l;
-    };
-    auto load = [&](const int c, uint32_t (&w)[WN]) {
-      const uint32_t *col = a.codes + (size_t)max(c, 0) * WN * NT + tid;
+      int l = 0;
 #pragma unroll
-      for (int q = 0; q < WN; ++q) w[q] = col[q * NT];
+      for (int q = 0; q < B; ++q) {              // absent columns repeat the last one, times zero
+        const bool there = left != 0;
+        l = there ? __builtin_ctzll(left) : l;
+        left &= left - 1;
+        bs[q] = there ? read_lane_f64(bsl, l) : 0.0;
+        m[q] = read_lane_f64(mul64, l);
+        const uint32_t *col = a.codes + (size_t)(base + l) * WN * NT + tid;
+#pragma unroll
+        for (int k = 0; k < WN; ++k) w[q][k] = col[k * NT];
+      }
+      return true;
     };
-    int c[B], cn[B];
     double bs[B], bn[B], m[B], mn[B];
     uint32_t w[B][WN], wn[B][WN];
+    bool more = group(bs, m, w);
+    while (more) {
+      more = group(bn, mn, wn);
 #pragma unroll
-    for (int q = 0; q < B; ++q) {
-      c[q] = next(bs[q], m[q]);
-      load(c[q], w[q]);
-    }
-    while (c[0] >= 0) {
-#pragma unroll
-      for (int q = 0; q < B; ++q) {
-        cn[q] = next(bn[q], mn[q]);
-        load(cn[q], wn[q]);
-      }
-#pragma unroll
-      for (int q = 0; q < B; ++q) {
-        if (c[q] < 0) continue;                  // uniform
+      for (int q = 0; q < B; ++q)
 #pragma unroll
         for (int r = 0; r < R; ++r) eta[r] = fma(bs[q], centred_at<R>(w[q], r, m[q]), eta[r]);
-      }
 #pragma unroll
       for (int q = 0; q < B; ++q) {
-        c[q] = cn[q];
         bs[q] = bn[q];
         m[q] = mn[q];
 #pragma unroll
@@ -265,17 +258,60 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
     }
   };
 
-  // a coefficient moves by delta (uniform)
-  auto move = [&](const double delta, const double dmu, const double dis, const uint32_t (&wd)[WN]) {
-    // lanes 0..3 put the genotypes' factors in the wave's table (code 3, padded: 1); a wave's
-    // LDS accesses are processed in order, and the wave barrier keeps the compiler from
-    // moving the table reads above the write
-    if (lane < 4) cltab[wave][lane] = lane == 3 ? 1.0 : exp(-delta * ((static_cast<double>(lane) - dmu) * dis));
-    __builtin_amdgcn_wave_barrier();
+  // one wave per SIMD and few individuals per thread: a move's factors are selected from registers
+  constexpr bool SELECT = R <= 4 && NW <= 4;
+  // the standardised value of code 0, 1, 2 in lanes 0..2 (SELECT: of each four), zero in lane 3
+  auto code_values = [&](const double cmu, const double cis) {
+    const int code = SELECT ? lane & 3 : lane;
+    return code < 3 ? (static_cast<double>(code) - cmu) * cis : 0.0;
+  };
+  // a coefficient moves by delta (the same in every lane); xc: its column's code_values
+  auto move = [&](const double delta, const double xc, const uint32_t (&wd)[WN]) {
+    // SELECT: the factors broadcast in each four lanes and selected (padded individuals: any of them, E is infinite); n = 1000, p = 100, every
+    // coefficient non-zero, 0.82 -> 0.73 us per update.  Else lanes 0..3 put them in the wave's
+    // table (1 for code 3; n = 2000: 1.00 us, selected 1.08); a wave's LDS accesses are processed in
+    // order, and the wave barrier keeps the compiler from moving the table reads above the write
+    double f0 = 0.0, f1 = 0.0, f2 = 0.0;
+    if constexpr (SELECT) {
+      const double factor = exp(-delta * xc);
+      f0 = dpp_move_f64<0x00>(factor);
+      f1 = dpp_move_f64<0x55>(factor);
+      f2 = dpp_move_f64<0xAA>(factor);
+    } else {
+      if (lane < 4) cltab[wave][lane] = exp(-delta * xc);
+      __builtin_amdgcn_wave_barrier();
+    }
+    // in stages over U individuals: the table reads in flight together and the chains of E and u
+    // side by side (left alone, the scheduler takes the individuals one after the other, a wait
+    // for LDS each: n = 1000, p = 100, every coefficient non-zero, 0.91 us per update)
+    constexpr int U = R <= 10 ? R : R / 2;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      E[r] *= cltab[wave][code_at<R>(wd, r)];
-      u[r] = yk[r] - inv1p(E[r]);
+    for (int r0 = 0; r0 < R; r0 += U) {
+      double d[U], q[U];
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        if constexpr (SELECT) {
+          const uint32_t at = wd[0] >> (2 * (r0 + r));
+          d[r] = (at & 2u) ? f2 : (at & 1u) ? f1 : f0;
+        } else {
+          d[r] = cltab[wave][code_at<R>(wd, r0 + r)];
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < U; ++r) {
+        E[r0 + r] *= d[r];
+        d[r] = inv1p_arg(E[r0 + r]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < U; ++r) q[r] = __builtin_amdgcn_rcp(d[r]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < U; ++r) d[r] = fma(-d[r], q[r], 1.0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < U; ++r) u[r0 + r] = yk[r0 + r] - fma(q[r], d[r], q[r]);
     }
   };
   int parity = 0, tag = -1;                      // tag: the block whose column this lane's slot holds
@@ -357,7 +393,9 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
                 for (int k = 0; k < WN; ++k) w0[k] = slots[((slot0 + f + 1) * WN + k) * NT + tid];
               }
               const double fmu = read_lane_f64(mu, f), fis = read_lane_f64(is, f), fthr = read_lane_f64(thr, f);
-              const double fb = read_lane_f64(b, f);
+              const double fb = read_lane_f64(b, f), scale = inv_n4 * fis;
+              double fx = code_values(fmu, fis);
+              if constexpr (SELECT) asm volatile("" : "+v"(fx));   // formed here, not after the decision
               double g = 0.0;
 #pragma unroll
               for (int r = 0; r < R; ++r) g = fma(centred_at<R>(w, r, fmu), u[r], g);
@@ -374,17 +412,17 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
                 if constexpr (NW == 8) t += dpp_move_f64<0x141>(t);
                 parity ^= 1;
               }
-              const double gs = inv_n4 * (t * fis), z = fb + gs;
+              const double z = fma(scale, t, fb);   // t, and so delta, is the same in every lane
               const double nb = z > fthr ? z - fthr : (z < -fthr ? z + fthr : 0.0);
-              const double delta = read_lane_f64(nb - fb, 0);
+              const double delta = nb - fb;
               if (lane == f) {
-                g4f = fabs(gs);
+                g4f = fabs(scale * t);
                 at4f = path;
                 bf = nb;
               }
-              if (delta != 0.0) {
+              if (__any(delta != 0.0)) {
                 path += fabs(delta);
-                move(delta, fmu, fis, w);
+                move(delta, fx, w);
               }
               if (!more) break;
               ++f;
@@ -467,7 +505,7 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
             uint32_t wd[WN];
 #pragma unroll
             for (int k = 0; k < WN; ++k) wd[k] = slots[((slot0 + last) * WN + k) * NT + tid];
-            move(delta, dmu, dis, wd);
+            move(delta, code_values(dmu, dis), wd);
           }
         }
         if (wave == 0 && in) {                   // every wave holds the same values
@@ -595,9 +633,10 @@ template <typename IT>
 hipError_t launch_em_t(const MapArgs &a, hipStream_t st) {
   const int R = map_rows(a.n_pad);
   switch (map_threads(a.n_pad)) {
-    case 64: return R == 2 ? launch_em_r<IT, 64, 2>(a, st) : launch_em_r<IT, 64, 4>(a, st);
-    case 128: return launch_em_r<IT, 128, 4>(a, st);
-    case 256: return launch_em_r<IT, 256, 4>(a, st);
+    case 64:
+      return R == 1 ? launch_em_r<IT, 64, 1>(a, st)
+                    : R == 2 ? launch_em_r<IT, 64, 2>(a, st) : launch_em_r<IT, 64, 4>(a, st);
+    case 256: return R == 2 ? launch_em_r<IT, 256, 2>(a, st) : launch_em_r<IT, 256, 4>(a, st);
   }
   switch (R) {
     case 4: return launch_em_r<IT, 512, 4>(a, st);
