@@ -31,8 +31,10 @@
 // when it was last formed, plus the path length sum |delta| of the moves since stays below its
 // threshold 4 w_j / n is certain to stay zero: its update is decided without forming g_j.  What
 // the fresh predictor of a sweep changes in u (rounding, or products that had left the range of
-// a double) is measured and counts as path; kMargin covers the rounding of g_j itself; a NaN or
-// an infinity fails the comparison, so its columns are looked at.  Close to a mode the moves are
+// a double) is measured and counts as path.  The path is rounded up at every addition and starts
+// again from zero at each E step (what has been walked is added to the columns' |4 g_j / n|), so
+// that moves far below it still count; kMargin covers the rounding of g_j and of u; a NaN or an
+// infinity fails the comparison, so its columns are looked at.  Close to a mode the moves are
 // small and nearly all zero coefficients are decided so.
 //
 // Runs of columns.  An update that leaves beta_j as it was does not change u, so the gradients
@@ -157,8 +159,16 @@ __device__ __forceinline__ double wave_sums(const double (&v)[V], int label) {
   return c;
 }
 
-// 4 g_j / n is a sum of n terms of mean size below 4 in a tree: rounding below 1e-13.
+// What |4 g_j / n| may be off by within a sweep.  Its own sum, at most 20 terms per thread and 9
+// levels: 32 eps 4 mean |x u| <= 1.5e-14, eps = 2^-53, as mean |x u| <= 1 whatever the allele
+// frequency (mean x^2 = 1).  E and u, each rounded by less than 3 eps per move: 12 eps a move,
+// 7e-13 in the at most 512 of a sweep (the next predictor measures and counts what there was).
 constexpr double kMargin = 1e-12;
+// a + d for a, d >= 0, not below the sum.
+__device__ __forceinline__ double add_up(double a, double d) {
+  const double s = a + d;
+  return fma(s, 0x1p-51, s);
+}
 // Columns per block (and slots, where the columns do not all fit), and LDS bytes of the slots.
 constexpr int map_block(int R) { return map_words(R) == 1 ? 64 : 32; }
 constexpr size_t kMapSlotBytes = size_t(128) << 10;
@@ -315,13 +325,17 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
     }
   };
   int parity = 0, tag = -1;                      // tag: the block whose column this lane's slot holds
-  double path = 0.0;                             // sum of |delta| so far (uniform)
+  double path = 0.0;                             // sum of |delta| since the E step (uniform)
   for (int it = 0; it < a.outer; ++it) {
     for (int sw = 0; sw < a.inner; ++sw) {
       __syncthreads();                           // the previous sweep's coefficients
       if (sw == 0) {                             // E step: |4 w_j / n| thresholds of this M step
-        for (int j = tid; j < p; j += NT)
+        for (int j = tid; j < p; j += NT) {
           tl[j] = inv_n4 * (pr.inf ? 1.0 / pr.lam : (pr.a + 1.0) / (pr.a * pr.lam + fabs(bl[j])));
+          gl[j] = add_up(gl[j], path - pl[j]);
+          pl[j] = 0.0;
+        }
+        path = 0.0;
         __syncthreads();
       }
       {
@@ -343,7 +357,7 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
 #pragma unroll
           for (int k = 1; k < NW; ++k) drift += red[k];
         }
-        path += 4.0 * drift;
+        if (it + sw > 0) path = add_up(path, 4.0 * drift);   // (the first one starts from nothing)
       }
       for (int blk = 0; blk * BS < p; ++blk) {
         const int c0 = blk * BS, col = min(c0 + lane, p - 1);
@@ -356,7 +370,7 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
         uint32_t w0[WN];
         // the block's remaining candidates, their words in LDS and the first one's words on their way
         auto scan = [&]() -> unsigned long long {
-          look = in && lane >= pos && !(b == 0.0 && g4 + (path - at4) + kMargin <= thr);
+          look = in && lane >= pos && !(b == 0.0 && add_up(g4, path - at4) + kMargin <= thr);
           const unsigned long long c = __ballot(look);
           if (c == 0) return c;
           if (!resident) {                       // words that are not in their slot: one wait for all
@@ -421,7 +435,7 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
                 bf = nb;
               }
               if (__any(delta != 0.0)) {
-                path += fabs(delta);
+                path = add_up(path, fabs(delta));
                 move(delta, fx, w);
               }
               if (!more) break;
@@ -498,7 +512,7 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
             b = nb;
           }
           const double delta = moved ? read_lane_f64(d, last) : 0.0;
-          path += fabs(delta);
+          if (moved) path = add_up(path, fabs(delta));
           cand = scan();                         // its LDS reads run beside the move
           if (moved) {                           // uniform: column c0 + last moves by delta
             const double dmu = read_lane_f64(mu, last), dis = read_lane_f64(is, last);
