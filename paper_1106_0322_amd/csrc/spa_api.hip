@@ -73,10 +73,11 @@ struct XPack {
   bool ready = false;
 };
 
-// Genotype codes of the streamed FP32/FP64 contraction.
+// Genotype codes of the streamed FP32/FP64 contraction, and of its FP64 adjoint (packed when
+// the first gradient asks; the FP32 adjoint is tiled and has none).
 struct SPack {
   uint32_t *Xb = nullptr, *Xtb = nullptr;
-  bool ready = false;
+  bool ready = false, adjoint = false;
 };
 
 struct OpScratch {
@@ -306,15 +307,20 @@ spa_status ensure_xpack(spa_smc *h, Prec prec) {
   return SPA_OK;
 }
 
-spa_status ensure_spack(spa_smc *h, Prec prec) {
+spa_status ensure_spack(spa_smc *h, Prec prec, bool adjoint = false) {
   SPack &x = h->sp[static_cast<int>(prec)];
-  if (x.ready) return SPA_OK;
   spa_status st;
   const size_t bytes = stream_bytes(h->n, h->p);
-  if ((st = dalloc(h, &x.Xb, bytes)) != SPA_OK) return st;
-  if ((st = dalloc(h, &x.Xtb, bytes)) != SPA_OK) return st;
-  SPA_CK(h, launch_stream_pack(prec == Prec::F64, h->dX, h->n, h->p, x.Xb, x.Xtb, h->stream));
-  x.ready = true;
+  if (!x.ready) {
+    if (!x.Xb && (st = dalloc(h, &x.Xb, bytes)) != SPA_OK) return st;
+    SPA_CK(h, launch_stream_pack(h->dX, h->n, h->p, x.Xb, h->stream));
+    x.ready = true;
+  }
+  if (adjoint && !x.adjoint) {
+    if (!x.Xtb && (st = dalloc(h, &x.Xtb, bytes)) != SPA_OK) return st;
+    SPA_CK(h, launch_stream_pack_adjoint(h->dX, h->n, h->p, x.Xtb, h->stream));
+    x.adjoint = true;
+  }
   return SPA_OK;
 }
 
@@ -469,7 +475,7 @@ StreamArgs stream_args_core(const spa_smc *h, Prec prec, int M, bool grad, int s
 spa_status run_stream(spa_smc *h, Prec prec, const void *beta, int beta_f64, const OpScratch *o, int M, bool grad,
                       int smax, double *ll, StreamArgs *out) {
   spa_status st;
-  if ((st = ensure_spack(h, prec)) != SPA_OK) return st;
+  if ((st = ensure_spack(h, prec, grad)) != SPA_OK) return st;
   StreamArgs a = stream_args_core(h, prec, M, grad, smax);
   a.beta = beta;
   a.beta_f64 = beta_f64;
@@ -1169,7 +1175,7 @@ extern "C" spa_status spa_smc_init(const spa_smc_config *cfg, const uint8_t *X_h
   // the handle's own precision is always prepared, for its sweeps and for spa_smc_loglik_noalloc
   // (FP32 MALA: the tiled copy for the one, the streamed copy for the other)
   if (!h->f8_terms && tiled_sampler(h) && (st = ensure_xpack(h, h->prec)) != SPA_OK) return fail(st);
-  if (streamed(h->prec) && (st = ensure_spack(h, h->prec)) != SPA_OK) return fail(st);
+  if (streamed(h->prec) && (st = ensure_spack(h, h->prec, mala && h->prec == Prec::F64)) != SPA_OK) return fail(st);
   if (h->move == SPA_MOVE_SINGLE) {
     h->ss_rows = single_site_rows(n);   // n <= single_site_max_n() was checked above
     if ((st = dalloc(h, &h->xs_ss, h->psz * (size_t)p * h->ss_rows)) != SPA_OK) return fail(st);

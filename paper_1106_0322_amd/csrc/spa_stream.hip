@@ -67,23 +67,22 @@ constexpr int code_regs(int ND) { return ND <= 2 ? ND : (ND + 3) / 4 * 4; }
 // LDS row of 16 ND coefficients, padded so that 16 rows' consecutive entries hit distinct banks.
 constexpr int row_stride(int ND) { return 16 * ND + 4; }
 
-__global__ void stream_pack_kernel(bool f64, const uint8_t *__restrict__ X, int n, int p, int nblk, int stride,
-                                   uint32_t *__restrict__ Xb, uint32_t *__restrict__ Xtb) {
+template <bool ADJOINT>
+__global__ void stream_pack_kernel(const uint8_t *__restrict__ X, int n, int p, int nblk, int stride,
+                                   uint32_t *__restrict__ out) {
   const size_t total = (size_t)nblk * 64 * stride;
   for (size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x; idx < total;
        idx += (size_t)gridDim.x * blockDim.x) {
     const int d = static_cast<int>(idx % stride), lane = static_cast<int>(idx / stride % 64);
     const int ib = static_cast<int>(idx / stride / 64), lr = lane & 15, lg = lane >> 4;
-    uint32_t f = 0, t = 0;
+    uint32_t f = 0;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int k = ib * 16 + lr, j = 16 * d + 4 * q + lg;
+      const int k = ib * 16 + (ADJOINT ? ST<Prec::F64>::crow(lg, q) : lr);
+      const int j = 16 * d + (ADJOINT ? lr : 4 * q + lg);
       if (k < n && j < p) f |= static_cast<uint32_t>(X[(size_t)k * p + j]) << (8 * q);
-      const int kt = ib * 16 + (f64 ? lg + 4 * q : 4 * lg + q), jt = 16 * d + lr;
-      if (kt < n && jt < p) t |= static_cast<uint32_t>(X[(size_t)kt * p + jt]) << (8 * q);
     }
-    Xb[idx] = f;
-    Xtb[idx] = t;
+    out[idx] = f;
   }
 }
 
@@ -757,12 +756,19 @@ double block_clocks(Prec prec, int p, bool grad) {
 
 }  // namespace
 
-hipError_t launch_stream_pack(bool f64, const uint8_t *X, int n, int p, uint32_t *Xb, uint32_t *Xtb, hipStream_t s) {
+template <bool ADJOINT>
+static hipError_t launch_pack(const uint8_t *X, int n, int p, uint32_t *out, hipStream_t s) {
   const int nblk = stream_blocks(n), stride = stream_stride(p);
   const size_t total = (size_t)nblk * 64 * stride;
   const int grid = static_cast<int>(std::min<size_t>((total + 255) / 256, 8192));
-  hipLaunchKernelGGL(stream_pack_kernel, dim3(grid), dim3(256), 0, s, f64, X, n, p, nblk, stride, Xb, Xtb);
+  hipLaunchKernelGGL(stream_pack_kernel<ADJOINT>, dim3(grid), dim3(256), 0, s, X, n, p, nblk, stride, out);
   return hipGetLastError();
+}
+hipError_t launch_stream_pack(const uint8_t *X, int n, int p, uint32_t *Xb, hipStream_t s) {
+  return launch_pack<false>(X, n, p, Xb, s);
+}
+hipError_t launch_stream_pack_adjoint(const uint8_t *X, int n, int p, uint32_t *Xtb, hipStream_t s) {
+  return launch_pack<true>(X, n, p, Xtb, s);
 }
 
 int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
@@ -777,7 +783,7 @@ int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
 }
 
 hipError_t launch_stream(const StreamArgs &a, hipStream_t s) {
-  if (a.S < 1 || (a.S > 1 && !a.spl_part) || (a.grad && (!a.spl_part || !a.g_part))) return hipErrorInvalidValue;
+  if (a.S < 1 || (a.S > 1 && !a.spl_part) || (a.grad && (!a.spl_part || !a.g_part || !a.Xtb))) return hipErrorInvalidValue;
   if (a.prec == Prec::F64)
     return a.grad ? launch_width<Prec::F64, true>(a, s) : launch_width<Prec::F64, false>(a, s);
   if (a.prec == Prec::F32)

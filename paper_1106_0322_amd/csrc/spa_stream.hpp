@@ -13,8 +13,8 @@ namespace spa {
 //   Xb [(block * 64 + lane) * stride + d], byte q: code of individual lane % 16 of the
 //     block and marker 16 d + 4 q + lane / 16 (the lane's A operand of k-step 4 d + q);
 //   Xtb[(block * 64 + lane) * stride + d], byte v: code of the block's individual
-//     row(lane / 16, v) and marker 16 d + lane % 16 (row: the MFMA's output rows, 4 g + v in
-//     FP32 and g + 4 v in FP64), the A operands of the adjoint.
+//     lane / 16 + 4 v (the FP64 MFMA's output rows) and marker 16 d + lane % 16, the A operands of
+//     the FP64 adjoint.
 // Entries outside the n x p genotypes are 0.
 __host__ __device__ inline int stream_dwords(int p) { return (p + 15) / 16; }
 __host__ __device__ inline int stream_stride(int p) {   // dwords per lane and block: 4-, 8- or 16-byte loads
@@ -23,12 +23,13 @@ __host__ __device__ inline int stream_stride(int p) {   // dwords per lane and b
 }
 inline int stream_blocks(int n) { return (n + 15) / 16; }
 inline size_t stream_bytes(int n, int p) { return (size_t)stream_blocks(n) * 64 * 4 * stream_stride(p); }
-hipError_t launch_stream_pack(bool f64, const uint8_t *X, int n, int p, uint32_t *Xb, uint32_t *Xtb, hipStream_t s);
+hipError_t launch_stream_pack(const uint8_t *X, int n, int p, uint32_t *Xb, hipStream_t s);
+hipError_t launch_stream_pack_adjoint(const uint8_t *X, int n, int p, uint32_t *Xtb, hipStream_t s);
 
 struct StreamArgs {
   Prec prec;               // F32 or F64
   bool grad;
-  const uint32_t *Xb, *Xtb;
+  const uint32_t *Xb, *Xtb;   // Xtb: gradients only
   int n, p, M;
   // operand: the particles themselves (packed by the kernel), or, with beta null, the
   // rows written by the proposal step
