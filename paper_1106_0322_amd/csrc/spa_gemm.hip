@@ -1022,13 +1022,9 @@ static hipError_t launch_one(const GemmArgs &a, hipStream_t s) {
   constexpr size_t lds = Lds<P, PP, GRAD>::bytes;
   static_assert(lds <= 160 * 1024, "LDS budget of one CU");
   auto kern = loglik_kernel<P, PP, GRAD, FP8>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = raise_lds_limit(once, kern, lds);
+  if (e != hipSuccess) return e;
   constexpr int per_wg = Shape<P, PP>::WGP;
   const int tiles_p = (a.M + per_wg - 1) / per_wg;
   const int g8 = 8 / a.S;
@@ -1042,13 +1038,9 @@ static hipError_t launch_wide(const GemmArgs &a, hipStream_t s) {
   constexpr size_t lds = Wide<PP, FP8>::bytes;
   static_assert(lds <= 160 * 1024, "LDS budget of one CU");
   auto kern = loglik_wide_kernel<PP, FP8>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = raise_lds_limit(once, kern, lds);
+  if (e != hipSuccess) return e;
   const int tiles_p = (a.M + 63) / 64;
   const int g8 = 8 / a.S;
   const int grid = 8 * ((tiles_p + g8 - 1) / g8);

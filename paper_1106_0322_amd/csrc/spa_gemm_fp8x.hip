@@ -333,13 +333,9 @@ hipError_t launch_fp8x_one(const Fp8xArgs &a, hipStream_t st) {
   constexpr size_t lds = F8Shape<PP, NTERM>::bytes;
   static_assert(lds <= 160 * 1024, "LDS budget of one CU");
   auto kern = fp8x_loglik_kernel<PP, NTERM>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static OncePerDevice once;
+  const hipError_t e = raise_lds_limit(once, kern, lds);
+  if (e != hipSuccess) return e;
   constexpr int per_wg = F8Shape<PP, NTERM>::WGP;
   const int tiles_p = (a.M + per_wg - 1) / per_wg;
   const int g8 = 8 / a.S;

@@ -5,8 +5,23 @@
 #include <stdint.h>
 
 #include "../../include/spa_smc.h"
+#include "spa_once.hpp"
 
 namespace spa {
+
+// Raises the current device's limit of dynamic LDS for a kernel (each kernel has its own `once`).
+template <typename K>
+hipError_t raise_lds_limit(OncePerDevice &once, K kernel, size_t bytes) {
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  once.run(device, [&](int) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(bytes));
+    return e == hipSuccess;
+  });
+  return e;
+}
 
 enum class Prec : int { F64 = 0, F32 = 1, BF16X2 = 2 };
 

@@ -69,10 +69,10 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <atomic>
 #include <type_traits>
 
 #include "spa_common.hpp"
+#include "spa_internal.hpp"
 #include "spa_lanes.hpp"
 #include "spa_map.hpp"
 
@@ -632,13 +632,9 @@ hipError_t launch_em_r(const MapArgs &a, hipStream_t st) {
   const bool resident = map_resident(NT, R, a.p);
   const size_t column = (size_t)NT * map_words(R) * 4;
   const size_t lds = column * (resident ? a.p : map_block(R));
-  static std::atomic<bool> set{false};
-  if (!set.load(std::memory_order_relaxed)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMapSlotBytes);
-    if (e != hipSuccess) return e;
-    set.store(true, std::memory_order_relaxed);
-  }
+  static OncePerDevice once;
+  const hipError_t e = raise_lds_limit(once, kern, kMapSlotBytes);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(a.M), dim3(NT), lds, st, a, resident ? 1 : 0);
   return hipGetLastError();
 }

@@ -27,7 +27,6 @@
 // of the product of the lane's four factors 1 + e^-|eta|, less one, per block; both add per block in FP64,
 // then lane groups, waves and ranges in order.
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 
 #include "spa_lanes.hpp"
@@ -660,17 +659,6 @@ __global__ __launch_bounds__(64 * NW, P == Prec::F32 ? 4 : 2) void rwm_sweeps_ke
   }
 }
 
-template <typename K>
-hipError_t dynamic_lds(K kern, size_t bytes, std::atomic<bool> &set) {
-  if (!set.load(std::memory_order_relaxed)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e != hipSuccess) return e;
-    set.store(true, std::memory_order_relaxed);
-  }
-  return hipSuccess;
-}
-
 template <Prec P, int ND, bool GRAD, int NW, int TILES>
 hipError_t launch_waves(const StreamArgs &a, hipStream_t s) {
   using EL = typename ST<P>::EL;
@@ -679,8 +667,8 @@ hipError_t launch_waves(const StreamArgs &a, hipStream_t s) {
   constexpr size_t lds = rows > red ? rows : red;
   static_assert(lds <= 140 * 1024, "LDS budget");
   auto kern = stream_kernel<P, ND, GRAD, NW, TILES>;
-  static std::atomic<bool> set{false};
-  const hipError_t e = dynamic_lds(kern, lds, set);
+  static OncePerDevice once;
+  const hipError_t e = raise_lds_limit(once, kern, lds);
   if (e != hipSuccess) return e;
   const int tiles = (a.M + kStreamRows * TILES - 1) / (kStreamRows * TILES);
   hipLaunchKernelGGL(kern, dim3((unsigned)tiles * a.S), dim3(64 * NW), lds, s, a);
@@ -725,8 +713,8 @@ template <Prec P, int ND, int NW>
 hipError_t launch_rwm_one(const RwmArgs &a, hipStream_t s) {
   constexpr size_t lds = 16 * (size_t)row_stride(ND) * sizeof(typename ST<P>::EL);
   auto kern = rwm_sweeps_kernel<P, ND, NW>;
-  static std::atomic<bool> set{false};
-  const hipError_t e = dynamic_lds(kern, lds, set);
+  static OncePerDevice once;
+  const hipError_t e = raise_lds_limit(once, kern, lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((a.M + kStreamRows - 1) / kStreamRows), dim3(64 * NW), lds, s, a);
   return hipGetLastError();

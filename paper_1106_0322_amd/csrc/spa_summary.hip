@@ -22,9 +22,9 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <atomic>
 
 #include "spa_common.hpp"
+#include "spa_internal.hpp"
 #include "spa_summary.hpp"
 
 namespace spa {
@@ -555,14 +555,9 @@ template <typename VT, typename KT, int EPT, bool KEYS>
 static hipError_t launch_column(const SqArgs &a, int K, hipStream_t s) {
   auto kern = sq_column_kernel<VT, KT, EPT, KEYS>;
   const size_t lds = sizeof(unsigned long long) * kColStride * (size_t)a.lv.L;
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set.load(std::memory_order_relaxed)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)(sizeof(unsigned long long) * kColStride * kSqMaxLevels));
-    if (e != hipSuccess) return e;
-    attr_set.store(true, std::memory_order_relaxed);
-  }
+  static OncePerDevice once;
+  const hipError_t e = raise_lds_limit(once, kern, sizeof(unsigned long long) * kColStride * kSqMaxLevels);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(8 * ((a.p + 7) / 8)), dim3(kColThreads), lds, s,
                      reinterpret_cast<const VT *>(a.values), reinterpret_cast<const KT *>(a.keys), a.M, a.p, a.w, a.log_weights, K, a.q, a.lv, a.flag, a.quant,
                      a.conc);
