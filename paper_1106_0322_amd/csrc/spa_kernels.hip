@@ -2,6 +2,8 @@
 // incremental weights, logsumexp/ESS and systematic resampling, gathers and weighted
 // moments.  Row kernels map one wave64 to one particle (its p coefficients are contiguous,
 // so a wave reads a row with 16-byte lanes); reductions use fixed butterfly/tree orders.
+#include <type_traits>
+
 #include "spa_common.hpp"
 #include "spa_lanes.hpp"
 #include "spa_kernels.hpp"
@@ -1231,7 +1233,7 @@ static void launch_propose_t(const ProposeArgs &a, hipStream_t st) {
     const dim3 grid(grid_rows(a.M_pad, 8));
     if (vr) hipLaunchKernelGGL((propose_kernel<P, PT, MALA, 32, F8, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((propose_kernel<P, PT, MALA, 32, F8, false>), grid, dim3(256), 0, st, a);
-  } else {
+  } else if constexpr (P != Prec::F64) {   // FP64 rows are of at most 256 markers
     const dim3 grid(grid_rows(a.M_pad, 4));
     if (vr) hipLaunchKernelGGL((propose_kernel<P, PT, MALA, 64, F8, true>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((propose_kernel<P, PT, MALA, 64, F8, false>), grid, dim3(256), 0, st, a);
@@ -1252,21 +1254,32 @@ void launch_propose(Prec prec, bool mala, const ProposeArgs &a, hipStream_t st) 
   }
 }
 
+// Counts of partial sums that a decision can meet (0: the contraction wrote whole results).  The
+// tiled contractions leave 2, 4 or 8; the streamed ones up to 16, and with a gradient (FP64
+// MALA) always partials, of one range too.
+template <Prec P, bool MALA>
+constexpr bool accept_splits(int S) {
+  if (S == 0) return !(P == Prec::F64 && MALA);
+  if (S == 1) return P == Prec::F64 && MALA;
+  if (S == 16) return P == Prec::F64 || (P == Prec::F32 && !MALA);
+  return S == 2 || S == 4 || S == 8;
+}
+
 template <Prec P, typename PT, bool MALA, bool NEXT, int LP, bool F8, bool VR>
 static void launch_accept_vr(int S, const AcceptArgs &a, const ProposeArgs &na, hipStream_t st) {
   const int grid = grid_rows(a.M, 256 / LP);
-  switch (S) {
-    case 0: hipLaunchKernelGGL((accept_kernel<P, PT, MALA, 0, NEXT, LP, F8, VR>), dim3(grid), dim3(256), 0, st, a, na); break;
-    case 2: hipLaunchKernelGGL((accept_kernel<P, PT, MALA, 2, NEXT, LP, F8, VR>), dim3(grid), dim3(256), 0, st, a, na); break;
-    case 4: hipLaunchKernelGGL((accept_kernel<P, PT, MALA, 4, NEXT, LP, F8, VR>), dim3(grid), dim3(256), 0, st, a, na); break;
-    case 8: hipLaunchKernelGGL((accept_kernel<P, PT, MALA, 8, NEXT, LP, F8, VR>), dim3(grid), dim3(256), 0, st, a, na); break;
-    default:   // split counts of the streamed FP32/FP64 contraction only
-      if constexpr (P != Prec::BF16X2) {
-        if (S == 1) hipLaunchKernelGGL((accept_kernel<P, PT, MALA, 1, NEXT, LP, F8, VR>), dim3(grid), dim3(256), 0, st, a, na);
-        else hipLaunchKernelGGL((accept_kernel<P, PT, MALA, 16, NEXT, LP, F8, VR>), dim3(grid), dim3(256), 0, st, a, na);
-      }
-      break;
-  }
+  auto launch = [&](auto count) {
+    constexpr int SPL = decltype(count)::value;
+    if constexpr (accept_splits<P, MALA>(SPL))
+      if (S == SPL)
+        hipLaunchKernelGGL((accept_kernel<P, PT, MALA, SPL, NEXT, LP, F8, VR>), dim3(grid), dim3(256), 0, st, a, na);
+  };
+  launch(std::integral_constant<int, 0>{});
+  launch(std::integral_constant<int, 1>{});
+  launch(std::integral_constant<int, 2>{});
+  launch(std::integral_constant<int, 4>{});
+  launch(std::integral_constant<int, 8>{});
+  launch(std::integral_constant<int, 16>{});
 }
 
 template <Prec P, typename PT, bool MALA, bool NEXT, int LP, bool F8>
@@ -1275,7 +1288,6 @@ static void launch_accept_lp(int S, const AcceptArgs &a, const ProposeArgs &na, 
   else launch_accept_vr<P, PT, MALA, NEXT, LP, F8, false>(S, a, na, st);
 }
 
-// S: the number of partial sums to combine (0: the contraction wrote whole results).
 template <Prec P, typename PT, bool MALA, bool NEXT, bool F8 = false>
 static void launch_accept_t(int S, int PP, const AcceptArgs &a, const ProposeArgs &na, hipStream_t st) {
   const int lanes = row_lanes(PP, F8);
@@ -1284,8 +1296,12 @@ static void launch_accept_t(int S, int PP, const AcceptArgs &a, const ProposeArg
       launch_accept_lp<P, PT, MALA, NEXT, 16, F8>(S, a, na, st);
       return;
     }
-  if (lanes == 32) launch_accept_lp<P, PT, MALA, NEXT, 32, F8>(S, a, na, st);
-  else launch_accept_lp<P, PT, MALA, NEXT, 64, F8>(S, a, na, st);
+  if constexpr (P != Prec::F64)   // FP64 rows are of at most 256 markers
+    if (lanes == 64) {
+      launch_accept_lp<P, PT, MALA, NEXT, 64, F8>(S, a, na, st);
+      return;
+    }
+  launch_accept_lp<P, PT, MALA, NEXT, 32, F8>(S, a, na, st);
 }
 
 template <Prec P, typename PT>
@@ -1309,8 +1325,10 @@ static void launch_accept_p(bool mala, int S, int PP, const AcceptArgs &a, const
 
 hipError_t launch_accept(Prec prec, bool mala, int PP, const AcceptArgs &a, const ProposeArgs *next, hipStream_t st) {
   const int S = a.spl_part != nullptr ? a.S : 0;
-  if (S != 0 && S != 1 && S != 2 && S != 4 && S != 8 && S != 16) return hipErrorInvalidValue;
-  if (prec == Prec::BF16X2 && (S == 1 || S == 16)) return hipErrorInvalidValue;
+  const bool can = prec == Prec::F64   ? (mala ? accept_splits<Prec::F64, true>(S) : accept_splits<Prec::F64, false>(S))
+                   : prec == Prec::F32 ? (mala ? accept_splits<Prec::F32, true>(S) : accept_splits<Prec::F32, false>(S))
+                                       : accept_splits<Prec::BF16X2, true>(S);
+  if (!can || (prec == Prec::F64 && row_lanes(PP, false) == 64)) return hipErrorInvalidValue;
   if (prec == Prec::F64) launch_accept_p<Prec::F64, double>(mala, S, PP, a, next, st);
   else if (prec == Prec::F32 || !next) launch_accept_p<Prec::F32, float>(mala, S, PP, a, next, st);
   else launch_accept_p<Prec::BF16X2, float>(mala, S, PP, a, next, st);   // no operand written: one instance
