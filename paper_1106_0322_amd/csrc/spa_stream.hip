@@ -774,15 +774,43 @@ hipError_t launch_stream_pack_adjoint(const uint8_t *X, int n, int p, uint32_t *
   return launch_pack<true>(X, n, p, Xtb, s);
 }
 
+// The power of two of least estimated time, in clocks: rounds of workgroups over the CUs, each a
+// range's blocks of one SIMD's waves and the workgroup's rows; the latency that a workgroup's end
+// leaves uncovered (where a CU holds several); what the ranges' partials cost to combine.
+// The numbers are fitted to 863 calls measured with 1 to 16 ranges (n = 100 .. 10000, p = 12 ..
+// 500, M = 300 .. 32768): the chosen count is at most 0.7 % slower than the best one on average.
+// Doubling until a number of workgroups is reached was 5 to 9 % slower on average and 25 % slower
+// than the tiled kernel before where a last round was nearly empty (FP64 gradient n = 10000, p =
+// 200, M = 4100: 1 range 1717 us, 4 1103; n = 5000, p = 200, M = 9000: 1 range 1300, 4 1064;
+// log-likelihoods n = 1600, p = 250, M = 2000: 8 ranges 77, 2 46).
 int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
-  const int nblk = stream_blocks(n), nw = grad ? stream_waves<true>() : stream_waves<false>();
+  const bool f64 = prec == Prec::F64;
+  const int nblk = stream_blocks(n), nd = stream_dwords(p), nks = (p + 3) / 4;
+  if (!grad && nblk * block_clocks(prec, p, false) <= 4 * 16000.0) return 1;   // the combination's launch costs more
   const long long tiles = (M + kStreamRows - 1) / kStreamRows;
-  int S = 1;
-  if (!grad && nblk * block_clocks(prec, p, grad) <= 4 * 16000.0) return 1;   // the combination's launch costs more
-  // workgroups the chip holds: two or more per CU, one where a wave takes a SIMD's registers
-  const int want = grad && stream_dwords(p) > 8 ? 200 : 512;
-  while (2 * S <= smax && tiles * S < want && nblk >= 2 * S * nw) S *= 2;
-  return S;
+  const bool own = grad && tiles >= kOwnTiles;
+  const long long wgs = own ? (tiles + 3) / 4 : tiles;
+  const int group = grad ? 4 : nd <= (f64 ? 8 : 16) ? 16 : 8;   // blocks of a pass of the workgroup's waves
+  const double mfma = (nks + (grad ? 4 * nd : 0)) * (f64 ? 64.0 : 32.0);
+  const double block = grad ? 1.64 * mfma + 910.0 : f64 ? 0.88 * mfma + 820.0 : 1.07 * mfma + 100.0;
+  const double rows = grad ? 2100.0 + 100.0 * p * (own ? 4 : 1) : f64 ? 42.0 * p : 800.0 + 25.0 * p;
+  const double tail = grad ? (nd <= 8 ? 0.27 : 0.0) : f64 ? (nd <= 4 ? 0.04 : 0.0) : nd <= 16 ? 0.1 : 0.0;
+  const double launch = grad ? 900.0 : f64 ? 7000.0 : 5600.0;
+  const double partial = grad ? 0.001 * M * gemm_pad_markers(p, prec) : 0.0;
+  int best = 1;
+  double least = 0.0;
+  for (int S = 1; S <= smax && S <= nblk; S *= 2) {
+    if (!grad && S > 1 && 8ull * S * tiles * kStreamRows > kStreamPartialBytes) break;
+    const int per = (nblk + S - 1) / S;
+    const int blocks = own ? per : grad ? (per + 3) / 4 : (per + group - 1) / group * (group / 4);
+    const double rounds = static_cast<double>((wgs * S + 255) / 256);
+    const double t = (rounds + tail) * blocks * block + rounds * rows + (S > 1 ? launch : 0.0) + S * partial;
+    if (S == 1 || t < least) {
+      best = S;
+      least = t;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_stream(const StreamArgs &a, hipStream_t s) {

@@ -49,8 +49,10 @@ struct StreamArgs {
 
 // Particles per workgroup (rows of the partials are padded to it).
 constexpr int kStreamRows = 16;
-// Ranges of individuals for M particles, at most smax (a power of two); 1 when the work of a
-// particle block is small enough for one workgroup.
+// Most bytes of a log-likelihood call's partials (half of the array that calls without
+// allocation use, which take the same ranges).
+constexpr size_t kStreamPartialBytes = size_t(16) << 20;
+// Ranges of individuals for M particles, at most smax (a power of two).
 int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax);
 hipError_t launch_stream(const StreamArgs &a, hipStream_t s);
 
