@@ -96,9 +96,14 @@ struct Lds {
   static constexpr int NT = Shape<P, PP>::NT;
   static constexpr int CPR = PP * (int)sizeof(LX) / 16;
   static constexpr int CPT = NT * (int)sizeof(LX) / 16;
+  // slots from row to row: the chunks of a BF16 row are permuted (row_swizzle); FP32 rows, of
+  // which a fragment reads single words, are padded to an odd stride instead: the word's
+  // address is then an immediate offset, where a permuted one costs two instructions beside
+  // each MFMA (gradients n = 5000, p = 40, M = 40000: padded 807 us, permuted 896)
+  static constexpr int CX = CPR + (P == Prec::F32 ? 1 : 0), CT = CPT + (P == Prec::F32 ? 1 : 0);
   static constexpr int NTHR = Shape<P, PP>::NTHR;
-  static constexpr int XSL = (NT * CPR + NTHR - 1) / NTHR * NTHR;
-  static constexpr int TSL = GRAD ? (PP * CPT + NTHR - 1) / NTHR * NTHR : 0;
+  static constexpr int XSL = (NT * CX + NTHR - 1) / NTHR * NTHR;
+  static constexpr int TSL = GRAD ? (PP * CT + NTHR - 1) / NTHR * NTHR : 0;
   static constexpr int STG = XSL + TSL;
   static constexpr size_t bytes = 2 * (size_t)STG * 16;
 };
@@ -146,7 +151,7 @@ __attribute__((amdgpu_waves_per_eu((Shape<P, PP>::NW / 4), (Shape<P, PP>::NW / 4
   constexpr int QB = (P == Prec::BF16X2) ? 2 : 1;   // blocks per adjoint k-step
   constexpr int NKS = PP / KS;   // k-steps of the forward contraction
   constexpr int NMB = PP / 16;   // 16-marker blocks of the adjoint
-  constexpr int CPR = L::CPR, CPT = L::CPT;
+  constexpr int CPR = L::CPR, CPT = L::CPT, CX = L::CX, CT = L::CT;
   constexpr int XSL = L::XSL, TSL = L::TSL, STG = L::STG;
   constexpr int NTHR = SH::NTHR;
   // what must stay on its side between two k-steps: everything, or all but vector and scalar
@@ -217,13 +222,15 @@ __attribute__((amdgpu_waves_per_eu((Shape<P, PP>::NW / 4), (Shape<P, PP>::NW / 4
   int xoff[NQX], toff[NQT];
 #pragma unroll
   for (int q = 0; q < NQX; ++q) {
-    const int sl = q * NTHR + tid, r = sl / CPR, c = (sl % CPR) ^ row_swizzle<CPR>(r);
-    xoff[q] = r < NT ? r * PP * (int)sizeof(XG) + c * 16 * (int)sizeof(XG) / (int)sizeof(LX) : 0;
+    const int sl = q * NTHR + tid, r = sl / CX, at = sl % CX;
+    const int c = CX == CPR ? at ^ row_swizzle<CPR>(r) : at;
+    xoff[q] = (r < NT && c < CPR) ? r * PP * (int)sizeof(XG) + c * 16 * (int)sizeof(XG) / (int)sizeof(LX) : 0;
   }
 #pragma unroll
   for (int q = 0; q < NQT; ++q) {
-    const int sl = q * NTHR + tid, r = sl / CPT, c = (sl % CPT) ^ row_swizzle<CPT>(r);
-    toff[q] = (GRAD && r < PP) ? r * n_pad * (int)sizeof(XG) + c * 16 * (int)sizeof(XG) / (int)sizeof(LX) : 0;
+    const int sl = q * NTHR + tid, r = sl / CT, at = sl % CT;
+    const int c = CT == CPT ? at ^ row_swizzle<CPT>(r) : at;
+    toff[q] = (GRAD && r < PP && c < CPT) ? r * n_pad * (int)sizeof(XG) + c * 16 * (int)sizeof(XG) / (int)sizeof(LX) : 0;
   }
   const uint8_t *gxk = reinterpret_cast<const uint8_t *>(args.Xk);
   const uint8_t *gxt = reinterpret_cast<const uint8_t *>(args.Xt);
@@ -354,8 +361,8 @@ __attribute__((amdgpu_waves_per_eu((Shape<P, PP>::NW / 4), (Shape<P, PP>::NW / 4
     }
     constexpr bool SPREAD = (P == Prec::BF16X2) && !FP8 && (NKS >= NQX) && (NMB >= 2 * NQT);
     if constexpr (!FP8 && !SPREAD) SPA_ISSUE(ntile0, stage ^ 1);
-    const uint4 *sX = smem + stage * STG;          // individual-major tile, CPR slots per row
-    const uint4 *sXt = sX + XSL;                   // marker-major tile, CPT slots per row
+    const uint4 *sX = smem + stage * STG;          // individual-major tile, CX slots per row
+    const uint4 *sXt = sX + XSL;                   // marker-major tile, CT slots per row
     // rows ib * 16 + lr and mb * 16 + lr: the swizzle is that of row lr, its low two bits
     // and the rest (which the k-step's chunk number does not reach and meets, respectively)
     const int fx_lo = row_swizzle<CPR>(lr) & 3, fx_hi = row_swizzle<CPR>(lr) & ~3;
@@ -375,10 +382,10 @@ __attribute__((amdgpu_waves_per_eu((Shape<P, PP>::NW / 4), (Shape<P, PP>::NW / 4
       // 500: 366 us with the looser rule, 315 us with this one, 361 us without either).  The MFMAs
       // of a block's hi and lo parts alternate with those of the other block.
       auto xfrag = [&](const int ks, const int b) -> FR {
-        const uint4 *row = sX + ((q * QB + b) * 16 + lr) * CPR;
+        const uint4 *row = sX + ((q * QB + b) * 16 + lr) * CX;
         // chunk 4 ks + lg (BF16); word lg of chunk ks (FP32)
         if constexpr (P == Prec::BF16X2) return *reinterpret_cast<const FR *>(row + ((4 * ks) ^ fx_hi) + (lg ^ fx_lo));
-        else return reinterpret_cast<const FR *>(row + (ks ^ (fx_hi | fx_lo)))[lg];
+        else return reinterpret_cast<const FR *>(row)[4 * ks + lg];
       };
       if constexpr (P == Prec::BF16X2) {
         static_assert(PB == 1, "one particle block per wave");
@@ -496,7 +503,7 @@ __attribute__((amdgpu_waves_per_eu((Shape<P, PP>::NW / 4), (Shape<P, PP>::NW / 4
 #pragma unroll
           for (int mb = 0; mb < NMB; ++mb) {
             // the marker-major copy holds individuals crow(lg, 0..3) at positions 4lg..4lg+3
-            const LX *row = reinterpret_cast<const LX *>(sXt + (mb * 16 + lr) * CPT + (lg ^ ft_lo));
+            const LX *row = reinterpret_cast<const LX *>(sXt + (mb * 16 + lr) * CT + lg);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
               const LX a = row[v];
