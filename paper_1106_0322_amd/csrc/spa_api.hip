@@ -877,7 +877,7 @@ spa_status record_map(spa_smc *h, int row) {
 }
 
 // Summary scratch for M values of p coefficients.
-spa_status ensure_sq(spa_smc *h, size_t M, int p, bool f64) {
+spa_status ensure_sq(spa_smc *h, size_t M, int p, int L, bool f64) {
   spa_status st;
   if (!h->sq_st && (st = dalloc(h, &h->sq_st, sizeof(SqState))) != SPA_OK) return st;
   if (h->sq_q_cap < M) {
@@ -886,7 +886,7 @@ spa_status ensure_sq(spa_smc *h, size_t M, int p, bool f64) {
     if ((st = dalloc(h, &h->sq_q, 8 * M)) != SPA_OK) return st;
     h->sq_q_cap = M;
   }
-  const bool columns = sq_one_launch(f64, static_cast<long long>(M));
+  const bool columns = sq_one_launch(f64, static_cast<long long>(M), p, L);
   if (columns && !sq_key_columns(f64, static_cast<long long>(M), p)) return SPA_OK;   // the rest in registers and LDS
   const size_t kb = M * (size_t)p * sq_key_bytes(f64);
   if (h->sq_keys_cap < kb) {
@@ -914,7 +914,7 @@ spa_status ensure_sq(spa_smc *h, size_t M, int p, bool f64) {
 spa_status run_summaries(spa_smc *h, const void *values, bool f64, int M, int p, const double *w, bool logw,
                          const SqLevels &lv, double *quant, double *conc, int *flag = nullptr) {
   spa_status st;
-  if ((st = ensure_sq(h, (size_t)M, p, f64)) != SPA_OK) return st;
+  if ((st = ensure_sq(h, (size_t)M, p, lv.L, f64)) != SPA_OK) return st;
   SqArgs a{};
   a.values = values;
   a.f64 = f64;
@@ -1581,7 +1581,7 @@ extern "C" spa_status spa_weighted_summaries(spa_smc *h, const void *values_dev,
   if ((st = run_summaries(h, values_dev, values_are_fp64 != 0, M, p, w_dev, false, lv, quant_dev, conc_dev, flag)) !=
       SPA_OK)
     return st;
-  if (!sq_one_launch(values_are_fp64 != 0, M))
+  if (!sq_one_launch(values_are_fp64 != 0, M, p, lv.L))
     SPA_CK(h, hipMemcpyAsync(flag, &h->sq_st->flags, sizeof(int), hipMemcpyDeviceToHost, h->stream));
   SPA_CK(h, hipStreamSynchronize(h->stream));
   tflush(h);

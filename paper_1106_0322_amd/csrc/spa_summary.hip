@@ -273,12 +273,13 @@ __global__ __launch_bounds__(kColThreads) void sq_column_kernel(const VT *__rest
       }
     } else {
       // few values still match a level: one comparison per value and level, and the digit
-      // only for a wave that holds a match
+      // only for a wave that holds a match (threads beyond M repeat the last value with no weight:
+      // their additions of nothing to one bucket were most of a call at M = 1)
       for (int l = 0; l < lv.L; ++l) {
         const KT pre = static_cast<KT>(spre[l]);
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
-          if ((key[e] >> hi) == pre) {
+          if ((key[e] >> hi) == pre && q[e] != 0) {
             const int b = static_cast<int>(key[e] >> lo) & ((1 << width) - 1);
             atomicAdd(&hist[l * kColStride + b + (b >> 5)], static_cast<unsigned long long>(q[e]));
           }
@@ -368,24 +369,31 @@ __global__ __launch_bounds__(kPrepThreads) void sq_prepare_kernel(const double *
 }
 
 // Transpose values (M x p row-major) into key columns (p x M), and count the quantised
-// weight of |v| < Delta_d per coefficient (exact integer sums, any order).  A workgroup
-// takes kKeyTiles tiles of 32 rows and adds its sums to the totals once (one addition per
-// 32 rows spent 96 us on the contended atomics at M = 16384, p = 200, most of the pass).
-constexpr int kKeyTiles = 16;
+// weight of |v| < Delta_d per coefficient (exact integer sums, any order).  A workgroup takes
+// `per` tiles of 32 rows and adds its sums to the totals once, so that a total is added to by 64
+// workgroups or so (one addition per 32 rows spent 96 us on the contended atomics at M = 16384, p =
+// 200, most of the pass); one tile where no tolerance is given and nothing is added (M = 33000,
+// p = 40, one level: the call 125 us with 16 tiles, 103 with one).
+constexpr int kKeyAdds = 64, kKeyTilesMax = 16;
+inline int key_tiles(int M, int D) {
+  return D > 0 ? std::min(kKeyTilesMax, std::max(1, (M + 31) / 32 / kKeyAdds)) : 1;
+}
 
-template <typename VT, typename KT>
+template <typename VT, typename KT, bool CONC>   // CONC: any tolerances
 __global__ void sq_keys_kernel(const VT *__restrict__ vals, int M, int p, const uint64_t *__restrict__ q,
-                               SqLevels lv, KT *__restrict__ keys, unsigned long long *__restrict__ inside) {
+                               SqLevels lv, int per, KT *__restrict__ keys,
+                               unsigned long long *__restrict__ inside) {
   __shared__ VT tile[32][33];
   const int j0 = blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 32 x 8 threads
-  uint64_t in[4][kSqMaxLevels];                             // this thread's columns ty, ty + 8, ...
+  constexpr int ND = CONC ? kSqMaxLevels : 0;
+  uint64_t in[4][CONC ? kSqMaxLevels : 1];                  // this thread's columns ty, ty + 8, ...
 #pragma unroll
   for (int c = 0; c < 4; ++c)
 #pragma unroll
-    for (int d = 0; d < kSqMaxLevels; ++d) in[c][d] = 0;
-  for (int it = 0; it < kKeyTiles; ++it) {
-    const int i0 = (blockIdx.x * kKeyTiles + it) * 32;
+    for (int d = 0; d < ND; ++d) in[c][d] = 0;
+  for (int it = 0; it < per; ++it) {
+    const int i0 = (blockIdx.x * per + it) * 32;
     if (i0 >= M) break;
     __syncthreads();                                        // the previous tile has been read
     for (int r = ty; r < 32; r += 8) {
@@ -394,14 +402,14 @@ __global__ void sq_keys_kernel(const VT *__restrict__ vals, int M, int p, const 
     }
     __syncthreads();
     const int i = i0 + tx;
-    const uint64_t qi = i < M ? q[i] : 0ull;
+    const uint64_t qi = CONC && i < M ? q[i] : 0ull;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int j = j0 + ty + 8 * c;
       const VT v = tile[tx][ty + 8 * c];
       if (i < M && j < p) keys[(size_t)j * M + i] = key_of(v);
 #pragma unroll
-      for (int d = 0; d < kSqMaxLevels; ++d)
+      for (int d = 0; d < ND; ++d)
         if (d < lv.D && fabs(static_cast<double>(v)) < lv.delta[d]) in[c][d] += qi;
     }
   }
@@ -410,7 +418,7 @@ __global__ void sq_keys_kernel(const VT *__restrict__ vals, int M, int p, const 
   for (int c = 0; c < 4; ++c) {
     const int j = j0 + ty + 8 * c;
 #pragma unroll
-    for (int d = 0; d < kSqMaxLevels; ++d) {
+    for (int d = 0; d < ND; ++d) {
       if (d >= lv.D) continue;
       uint64_t s = in[c][d];
 #pragma unroll
@@ -589,26 +597,42 @@ bool sq_key_columns(bool f64, long long M, int p) {
   return M > kColInline * kColThreads && (long long)p * sq_key_bytes(f64) > 128;
 }
 
-bool sq_one_launch(bool f64, long long M) { return M <= (long long)kColThreads * col_ept_max(f64); }
+// Whether one workgroup per coefficient summarises the set: it has to fit the registers, and
+// not to be of few values and many coefficients, where a workgroup costs the same for each
+// coefficient and the passes over all of them next to nothing.  The line is fitted to 592 calls
+// measured in both forms (M = 1 .. 16000, p = 5 .. 20000, 1 to 8 levels; 0.1 % slower than the
+// better form on average): M = 100 FP32, 8 levels and tolerances, p = 1000 85 us against 110 of
+// the passes, p = 8000 495 against 321; M = 1000, p = 20000, 3 levels 512 against 613.
+bool sq_one_launch(bool f64, long long M, int p, int L) {
+  if (M > (long long)kColThreads * col_ept_max(f64)) return false;
+  return p * (1.0 + 0.37 * L - (0.34 + 0.68 * L) * 1e-3 * static_cast<double>(M)) <= 6500.0 || p > 65535;
+}
 
 hipError_t launch_weighted_summaries(const SqArgs &a, hipStream_t s) {
   const int M = a.M, p = a.p, L = a.lv.L, D = a.lv.D;
   const int K = 63 - ceil_log2_ll(M);
-  if (sq_one_launch(a.f64, M))
+  if (sq_one_launch(a.f64, M, p, L))
     return a.f64 ? launch_columns<double, uint64_t>(a, K, s) : launch_columns<float, uint32_t>(a, K, s);
   hipLaunchKernelGGL(sq_init_kernel, dim3((p * kSqMaxLevels + 255) / 256), dim3(256), 0, s, p, a.sel,
                      a.inside, D);
   hipLaunchKernelGGL(sq_prepare_kernel, dim3(1), dim3(kPrepThreads), 0, s, a.w, M, a.log_weights, K, a.lv, a.q,
                      a.st);
-  const dim3 tg((M + 32 * kKeyTiles - 1) / (32 * kKeyTiles), (p + 31) / 32);
-  if (a.f64)
-    hipLaunchKernelGGL((sq_keys_kernel<double, uint64_t>), tg, dim3(256), 0, s,
-                       reinterpret_cast<const double *>(a.values), M, p, a.q, a.lv,
-                       reinterpret_cast<uint64_t *>(a.keys), a.inside);
-  else
-    hipLaunchKernelGGL((sq_keys_kernel<float, uint32_t>), tg, dim3(256), 0, s,
-                       reinterpret_cast<const float *>(a.values), M, p, a.q, a.lv,
-                       reinterpret_cast<uint32_t *>(a.keys), a.inside);
+  const int per = key_tiles(M, D);
+  const dim3 tg((M + 32 * per - 1) / (32 * per), (p + 31) / 32);
+  auto keys = [&](auto kern, auto *values, auto *out) {
+    hipLaunchKernelGGL(kern, tg, dim3(256), 0, s, values, M, p, a.q, a.lv, per, out, a.inside);
+  };
+  if (a.f64) {
+    const auto *v = static_cast<const double *>(a.values);
+    auto *out = static_cast<uint64_t *>(a.keys);
+    if (D > 0) keys(sq_keys_kernel<double, uint64_t, true>, v, out);
+    else keys(sq_keys_kernel<double, uint64_t, false>, v, out);
+  } else {
+    const auto *v = static_cast<const float *>(a.values);
+    auto *out = static_cast<uint32_t *>(a.keys);
+    if (D > 0) keys(sq_keys_kernel<float, uint32_t, true>, v, out);
+    else keys(sq_keys_kernel<float, uint32_t, false>, v, out);
+  }
   if (L > 0) {
     const int bits = a.f64 ? 64 : 32;
     const dim3 hg((M + kChunk - 1) / kChunk, p);

@@ -52,10 +52,9 @@ inline int ceil_log2_ll(long long m) {
 }
 
 int sq_key_bytes(bool f64);
-// Whether M values of one coefficient fit a workgroup's registers: the set is then
-// summarised without the sel, hist and inside scratch, and without the keys unless
-// sq_key_columns.
-bool sq_one_launch(bool f64, long long M);
+// Whether M values of p coefficients are summarised by a workgroup per coefficient, with L
+// levels: without the sel, hist and inside scratch, and without the keys unless sq_key_columns.
+bool sq_one_launch(bool f64, long long M, int p, int L);
 bool sq_key_columns(bool f64, long long M, int p);
 hipError_t launch_weighted_summaries(const SqArgs &a, hipStream_t s);
 hipError_t launch_mixture_weights(const double *log_z, int T, int N, const double *logW, double *w,
