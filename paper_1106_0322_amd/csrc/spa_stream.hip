@@ -236,6 +236,13 @@ constexpr int kOwnTiles = 1024;
 template <bool GRAD>
 constexpr int stream_waves() { return GRAD ? 4 : 8; }
 
+// Rows of which a workgroup of 8 waves fills a CU's registers.  With more blocks of particles than
+// CUs they run in workgroups of 4, two to a CU, one of which packs its rows while the other
+// contracts: log-likelihoods M = 32768, FP64 n = 130, p = 250 109 us in 8 waves, 82 in 4 (tiled kernel
+// before 103), FP32 n = 300, p = 500 165 and 140; with one block per CU 8 waves are up to 28 % faster.
+constexpr bool wide(Prec prec, int nd) { return nd > (prec == Prec::F64 ? 8 : 16); }
+constexpr int kCUs = 256;
+
 // TILES = 1: the workgroup's waves share one block of 16 particles; TILES = NW: each wave has
 // its own (many particles with a gradient: no sum over waves, no idle wave when the blocks
 // of individuals do not divide by NW).  The gradient of short rows leaves room for two waves
@@ -315,16 +322,26 @@ __global__ __launch_bounds__(64 * NW, GRAD && ND <= 8 ? 2 : 1) void stream_kerne
         }
       }
     } else {
-      const EL *B = static_cast<const EL *>(a.B);
+      EL v[RB][NJ];
+      const int il = min(r0 + rb + min(lane, RB - 1), a.M - 1);      // lane r: row r of the group
+      const EL mr = static_cast<EL>(a.moff[il]);
+      const double yr = a.yb[il];
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
-        const int i = r0 + rb + r;
-        for (int j = lane; j < W16; j += 64)
-          rows[(rb + r) * RS + j] = (i < a.M && j < p) ? B[(size_t)i * a.PP + j] : EL(0);
-        if (lane == 0) {
-          smoff[tw][rb + r] = i < a.M ? static_cast<EL>(a.moff[i]) : EL(0);
-          syb[tw][rb + r] = i < a.M ? a.yb[i] : 0.0;
+        const EL *row = static_cast<const EL *>(a.B) + (size_t)min(r0 + rb + r, a.M - 1) * a.PP;
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) v[r][q] = row[min(lane + 64 * q, p - 1)];
+      }
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int q = 0; q < NJ; ++q) {
+          const int j = lane + 64 * q;
+          if (j < W16) rows[(rb + r) * RS + j] = j < p ? v[r][q] : EL(0);
         }
+      if (lane < RB) {
+        smoff[tw][rb + lane] = mr;
+        syb[tw][rb + lane] = yr;
       }
     }
   }
@@ -699,6 +716,8 @@ hipError_t launch_one(const StreamArgs &a, hipStream_t s) {
   } else {
     if constexpr (ND <= 4)   // one range of few particles: twice the waves, half the latency
       if (a.S == 1 && tiles <= 256) return launch_waves<P, ND, GRAD, 16, 1>(a, s);
+    if constexpr (wide(P, ND))
+      if (tiles > kCUs) return launch_waves<P, ND, GRAD, 4, 1>(a, s);
     return launch_waves<P, ND, GRAD, stream_waves<GRAD>(), 1>(a, s);
   }
 }
@@ -751,10 +770,9 @@ hipError_t launch_rwm_width(const RwmArgs &a, hipStream_t s) {
 
 // Clocks of one block of 16 individuals against 16 particles on one SIMD: matrix
 // instructions and the elementwise step (a wave's, as issued).
-double block_clocks(Prec prec, int p, bool grad) {
-  const int nks = (p + 3) / 4, nd = (p + 15) / 16;
-  const double mf = prec == Prec::F64 ? 64.0 : 32.0, el = prec == Prec::F64 ? 1500.0 : 200.0;
-  return (nks + (grad ? 4 * nd : 0)) * mf + el;
+double block_clocks(Prec prec, int p) {
+  const int nks = (p + 3) / 4;
+  return prec == Prec::F64 ? nks * 64.0 + 1500.0 : nks * 32.0 + 200.0;
 }
 
 }  // namespace
@@ -786,11 +804,11 @@ hipError_t launch_stream_pack_adjoint(const uint8_t *X, int n, int p, uint32_t *
 int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
   const bool f64 = prec == Prec::F64;
   const int nblk = stream_blocks(n), nd = stream_dwords(p), nks = (p + 3) / 4;
-  if (!grad && nblk * block_clocks(prec, p, false) <= 4 * 16000.0) return 1;   // the combination's launch costs more
+  if (!grad && nblk * block_clocks(prec, p) <= 4 * 16000.0) return 1;   // the combination's launch costs more
   const long long tiles = (M + kStreamRows - 1) / kStreamRows;
   const bool own = grad && tiles >= kOwnTiles;
   const long long wgs = own ? (tiles + 3) / 4 : tiles;
-  const int group = grad ? 4 : nd <= (f64 ? 8 : 16) ? 16 : 8;   // blocks of a pass of the workgroup's waves
+  const int group = grad ? 4 : !wide(prec, nd) ? 16 : tiles > kCUs ? 4 : 8;   // blocks of a pass of the workgroup's waves
   const double mfma = (nks + (grad ? 4 * nd : 0)) * (f64 ? 64.0 : 32.0);
   const double block = grad ? 1.64 * mfma + 910.0 : f64 ? 0.88 * mfma + 820.0 : 1.07 * mfma + 100.0;
   const double rows = grad ? 2100.0 + 100.0 * p * (own ? 4 : 1) : f64 ? 42.0 * p : 800.0 + 25.0 * p;
@@ -803,7 +821,7 @@ int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
     if (!grad && S > 1 && 8ull * S * tiles * kStreamRows > kStreamPartialBytes) break;
     const int per = (nblk + S - 1) / S;
     const int blocks = own ? per : grad ? (per + 3) / 4 : (per + group - 1) / group * (group / 4);
-    const double rounds = static_cast<double>((wgs * S + 255) / 256);
+    const double rounds = static_cast<double>((wgs * S + kCUs - 1) / kCUs);
     const double t = (rounds + tail) * blocks * block + rounds * rows + (S > 1 ? launch : 0.0) + S * partial;
     if (S == 1 || t < least) {
       best = S;
@@ -861,7 +879,7 @@ bool rwm_one_launch(Prec prec, int n, int p, int M) {
   if ((prec != Prec::F32 && prec != Prec::F64) || p > 256) return false;
   // per sweep: a CU's workgroups one after another plus their row work, against the whole
   // chip at the split contraction's share of its rate plus three launches
-  const double wg = stream_blocks(n) * block_clocks(prec, p, false) / 4.0;
+  const double wg = stream_blocks(n) * block_clocks(prec, p) / 4.0;
   const double tiles = (M + kStreamRows - 1) / kStreamRows;
   const double one = std::ceil(tiles / 256.0) * wg + 5000.0;
   const double apart = tiles * wg / 256.0 / 0.7 + 40000.0;
