@@ -96,11 +96,14 @@ struct Lds {
   static constexpr int NT = Shape<P, PP>::NT;
   static constexpr int CPR = PP * (int)sizeof(LX) / 16;
   static constexpr int CPT = NT * (int)sizeof(LX) / 16;
-  // slots from row to row: the chunks of a BF16 row are permuted (row_swizzle); FP32 rows, of
-  // which a fragment reads single words, are padded to an odd stride instead: the word's
-  // address is then an immediate offset, where a permuted one costs two instructions beside
-  // each MFMA (gradients n = 5000, p = 40, M = 40000: padded 807 us, permuted 896)
-  static constexpr int CX = CPR + (P == Prec::F32 ? 1 : 0), CT = CPT + (P == Prec::F32 ? 1 : 0);
+  // slots from row to row: the chunks of a row are permuted (row_swizzle), or, in FP32 rows of up to
+  // 128 and of 384 markers, the stride is padded to an odd one.  An FP32 fragment reads single
+  // words, whose address is then an immediate offset, where a permuted one costs two
+  // instructions beside each MFMA; the permuted tiles are smaller and their adjoint reads free of
+  // conflicts (gradients, padded and permuted: n = 5000, p = 40, M = 40000 807 and 896 us, p = 300
+  // 4060 and 4160; p = 200 1725 and 1609; p = 511, M = 9000 1290 and 1129)
+  static constexpr bool PAD = P == Prec::F32 && (PP <= 128 || PP == 384);
+  static constexpr int CX = CPR + PAD, CT = CPT + PAD;
   static constexpr int NTHR = Shape<P, PP>::NTHR;
   static constexpr int XSL = (NT * CX + NTHR - 1) / NTHR * NTHR;
   static constexpr int TSL = GRAD ? (PP * CT + NTHR - 1) / NTHR * NTHR : 0;
@@ -385,7 +388,8 @@ __attribute__((amdgpu_waves_per_eu((Shape<P, PP>::NW / 4), (Shape<P, PP>::NW / 4
         const uint4 *row = sX + ((q * QB + b) * 16 + lr) * CX;
         // chunk 4 ks + lg (BF16); word lg of chunk ks (FP32)
         if constexpr (P == Prec::BF16X2) return *reinterpret_cast<const FR *>(row + ((4 * ks) ^ fx_hi) + (lg ^ fx_lo));
-        else return reinterpret_cast<const FR *>(row)[4 * ks + lg];
+        else if constexpr (L::PAD) return reinterpret_cast<const FR *>(row)[4 * ks + lg];
+        else return reinterpret_cast<const FR *>(row + (ks ^ (fx_hi | fx_lo)))[lg];
       };
       if constexpr (P == Prec::BF16X2) {
         static_assert(PB == 1, "one particle block per wave");
@@ -503,7 +507,7 @@ __attribute__((amdgpu_waves_per_eu((Shape<P, PP>::NW / 4), (Shape<P, PP>::NW / 4
 #pragma unroll
           for (int mb = 0; mb < NMB; ++mb) {
             // the marker-major copy holds individuals crow(lg, 0..3) at positions 4lg..4lg+3
-            const LX *row = reinterpret_cast<const LX *>(sXt + (mb * 16 + lr) * CT + lg);
+            const LX *row = reinterpret_cast<const LX *>(sXt + (mb * 16 + lr) * CT + (L::PAD ? lg : lg ^ ft_lo));
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
               const LX a = row[v];

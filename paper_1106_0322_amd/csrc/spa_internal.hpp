@@ -9,9 +9,11 @@
 
 namespace spa {
 
-// Raises the current device's limit of dynamic LDS for a kernel (each kernel has its own `once`).
+// Raises the current device's limit of dynamic LDS for a kernel (each kernel has its own `once`);
+// nothing is to be done up to the default limit.
 template <typename K>
 hipError_t raise_lds_limit(OncePerDevice &once, K kernel, size_t bytes) {
+  if (bytes <= size_t(64) << 10) return hipSuccess;
   int device = 0;
   hipError_t e = hipGetDevice(&device);
   if (e != hipSuccess) return e;

@@ -428,7 +428,8 @@ __global__ void stream_final_ll_kernel(const double *__restrict__ part, const do
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= M) return;
   double sp = 0.0;
-  for (int s = 0; s < S; ++s) sp += part[s * Mp + i];
+#pragma unroll 8
+  for (int s = 0; s < S; ++s) sp += part[s * Mp + i];            // eight loads in flight, added in order
   ll[i] = yb[i] - sp;
 }
 
@@ -754,6 +755,7 @@ hipError_t launch_rwm_one(const RwmArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+constexpr int kRwmMarkersF32 = 128;   // longest FP32 rows of the one-launch sweeps
 template <Prec P>
 hipError_t launch_rwm_width(const RwmArgs &a, hipStream_t s) {
   const int nd = stream_dwords(a.p);
@@ -763,8 +765,10 @@ hipError_t launch_rwm_width(const RwmArgs &a, hipStream_t s) {
   if (nd <= 2) return few ? launch_rwm_one<P, 2, 16>(a, s) : launch_rwm_one<P, 2, 8>(a, s);
   if (nd <= 4) return few && P == Prec::F32 ? launch_rwm_one<P, 4, 16>(a, s) : launch_rwm_one<P, 4, 8>(a, s);
   if (nd <= 8) return launch_rwm_one<P, 8, 8>(a, s);
-  if (nd <= 13) return launch_rwm_one<P, 13, 8>(a, s);
-  if (nd <= 16) return launch_rwm_one<P, 16, 8>(a, s);
+  if constexpr (P == Prec::F64) {
+    if (nd <= 13) return launch_rwm_one<P, 13, 8>(a, s);
+    if (nd <= 16) return launch_rwm_one<P, 16, 8>(a, s);
+  }
   return hipErrorInvalidValue;
 }
 
@@ -795,12 +799,12 @@ hipError_t launch_stream_pack_adjoint(const uint8_t *X, int n, int p, uint32_t *
 // The power of two of least estimated time, in clocks: rounds of workgroups over the CUs, each a
 // range's blocks of one SIMD's waves and the workgroup's rows; the latency that a workgroup's end
 // leaves uncovered (where a CU holds several); what the ranges' partials cost to combine.
-// The numbers are fitted to 863 calls measured with 1 to 16 ranges (n = 100 .. 10000, p = 12 ..
-// 500, M = 300 .. 32768): the chosen count is at most 0.7 % slower than the best one on average.
-// Doubling until a number of workgroups is reached was 5 to 9 % slower on average and 25 % slower
-// than the tiled kernel before where a last round was nearly empty (FP64 gradient n = 10000, p =
-// 200, M = 4100: 1 range 1717 us, 4 1103; n = 5000, p = 200, M = 9000: 1 range 1300, 4 1064;
-// log-likelihoods n = 1600, p = 250, M = 2000: 8 ranges 77, 2 46).
+// The numbers are fitted to 1046 calls measured with 1 to 64 ranges (n = 100 .. 10000, p = 12 .. 500,
+// M = 16 .. 32768): the chosen count is 0.2 % (FP64 gradient) and 2 % (log-likelihoods) slower than
+// the best one on average.  Doubling until a number of workgroups is reached was 5 to 9 % slower and
+// left a last round nearly empty (FP64 gradient n = 10000, p = 200, M = 4100: 1 range 1717 us, 4 1103,
+// tiled kernel before 1369; n = 5000, p = 200, M = 9000: 1 range 1300, 4 1064; log-likelihoods n = 1600,
+// p = 250, M = 2000: 8 ranges 77, 2 46).
 int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
   const bool f64 = prec == Prec::F64;
   const int nblk = stream_blocks(n), nd = stream_dwords(p), nks = (p + 3) / 4;
@@ -809,12 +813,15 @@ int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
   const bool own = grad && tiles >= kOwnTiles;
   const long long wgs = own ? (tiles + 3) / 4 : tiles;
   const int group = grad ? 4 : !wide(prec, nd) ? 16 : tiles > kCUs ? 4 : 8;   // blocks of a pass of the workgroup's waves
-  const double mfma = (nks + (grad ? 4 * nd : 0)) * (f64 ? 64.0 : 32.0);
-  const double block = grad ? 1.64 * mfma + 910.0 : f64 ? 0.88 * mfma + 820.0 : 1.07 * mfma + 100.0;
-  const double rows = grad ? 2100.0 + 100.0 * p * (own ? 4 : 1) : f64 ? 42.0 * p : 800.0 + 25.0 * p;
-  const double tail = grad ? (nd <= 8 ? 0.27 : 0.0) : f64 ? (nd <= 4 ? 0.04 : 0.0) : nd <= 16 ? 0.1 : 0.0;
-  const double launch = grad ? 900.0 : f64 ? 7000.0 : 5600.0;
-  const double partial = grad ? 0.001 * M * gemm_pad_markers(p, prec) : 0.0;
+  // whether a CU holds several workgroups, so that one's rows run beside another's blocks
+  const bool several = grad ? nd <= 8 : nd <= (f64 ? 4 : 16) || (wide(prec, nd) && tiles > kCUs);
+  const double mfma = (nks + (grad ? 4 * nd : 0)) * (f64 ? 64.0 : 32.0), rp = static_cast<double>(p) * (own ? 4 : 1);
+  const double block = grad ? 1.235 * mfma + 830.0 : f64 ? 1.224 * mfma + 1015.0 : 0.902 * mfma + 94.0;
+  const double rows = grad ? 670.0 + 96.0 * rp : f64 ? 1140.0 + 39.0 * rp : 1250.0 + 16.0 * rp;
+  const double tail = !several ? 0.0 : grad ? 0.54 : f64 ? 0.09 : 0.16;
+  const double again = !several ? 1.0 : grad ? 1.24 : f64 ? 0.70 : 0.78;   // a further round's rows
+  const double launch = grad ? 2200.0 : f64 ? 8100.0 : 5300.0;
+  const double partial = grad ? 375.0 + 0.0006 * M * gemm_pad_markers(p, prec) : f64 ? 240.0 + 0.018 * M : 80.0 + 0.0045 * M;
   int best = 1;
   double least = 0.0;
   for (int S = 1; S <= smax && S <= nblk; S *= 2) {
@@ -822,7 +829,8 @@ int stream_splits(Prec prec, bool grad, int n, int p, int M, int smax) {
     const int per = (nblk + S - 1) / S;
     const int blocks = own ? per : grad ? (per + 3) / 4 : (per + group - 1) / group * (group / 4);
     const double rounds = static_cast<double>((wgs * S + kCUs - 1) / kCUs);
-    const double t = (rounds + tail) * blocks * block + rounds * rows + (S > 1 ? launch : 0.0) + S * partial;
+    const double t = (rounds + tail) * blocks * block + (1.0 + again * (rounds - 1.0)) * rows +
+                     (S > 1 ? launch : 0.0) + S * partial;
     if (S == 1 || t < least) {
       best = S;
       least = t;
@@ -848,7 +856,8 @@ hipError_t launch_stream_finalize(const StreamFinal &f, hipStream_t s) {
     return hipGetLastError();
   }
   const Prior pr = f.prior ? *f.prior : Prior{};
-  // few particles: a wave each, one coefficient per lane (latency); else four per lane
+  // few particles: a wave each, one coefficient per lane (latency); else four per lane, or two for
+  // rows that do not end near a multiple of 256
   const int LP = a.M <= 2048 ? 64 : a.p <= 64 ? 16 : a.p <= 128 ? 32 : 64;
   const dim3 grid((unsigned)(((size_t)a.M * LP + 255) / 256));
 #define SPA_FG(GP, BT, GO, LPV, UV)                                                                                 \
@@ -858,6 +867,7 @@ hipError_t launch_stream_finalize(const StreamFinal &f, hipStream_t s) {
 #define SPA_FG_LP(GP, BT, GO)                          \
   do {                                                 \
     if (a.M <= 2048) SPA_FG(GP, BT, GO, 64, 1);        \
+    else if (a.p > 256) SPA_FG(GP, BT, GO, 64, 2);     \
     else if (LP == 16) SPA_FG(GP, BT, GO, 16, 4);      \
     else if (LP == 32) SPA_FG(GP, BT, GO, 32, 4);      \
     else SPA_FG(GP, BT, GO, 64, 4);                    \
@@ -875,14 +885,34 @@ hipError_t launch_stream_finalize(const StreamFinal &f, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Estimated clocks of a sweep in both forms: rounds of workgroups over the CUs, each its blocks of
+// individuals and its rows, against the split contraction at its best count of ranges plus the
+// proposal and decision launches and their passes over the rows.  Fitted to 982 workloads measured
+// in both forms (n = 60 .. 10000, p = 5 .. 250, N = 64 .. 32768): the chosen form is 0.02 % (FP32) and
+// 0.2 % (FP64) slower than the better one on average.  Per sweep (us), one launch and apart, near the
+// line: FP32 n = 6400, p = 60, N = 3000 42.5 and 41.8, n = 1600, p = 60, N = 9000 37.6 and 42.4; FP64 n =
+// 60, p = 120, N = 32768 82 and 90, n = 200, p = 250, N = 16384 107 and 93 (the first is taken); beyond it
+// FP32 n = 6400, p = 120, N = 1000 71 and 33, FP64 n = 6400, p = 250, N = 9000 907 and 670.  FP32 rows
+// of more than 128 markers spilled in one launch: apart was the better one, or within 1 %, in all of 133.
 bool rwm_one_launch(Prec prec, int n, int p, int M) {
-  if ((prec != Prec::F32 && prec != Prec::F64) || p > 256) return false;
-  // per sweep: a CU's workgroups one after another plus their row work, against the whole
-  // chip at the split contraction's share of its rate plus three launches
-  const double wg = stream_blocks(n) * block_clocks(prec, p) / 4.0;
-  const double tiles = (M + kStreamRows - 1) / kStreamRows;
-  const double one = std::ceil(tiles / 256.0) * wg + 5000.0;
-  const double apart = tiles * wg / 256.0 / 0.7 + 40000.0;
+  const bool f64 = prec == Prec::F64;
+  if ((!f64 && prec != Prec::F32) || p > (f64 ? 256 : kRwmMarkersF32)) return false;
+  const int nblk = stream_blocks(n), nd = stream_dwords(p), nks = (p + 3) / 4;
+  const int tiles = (M + kStreamRows - 1) / kStreamRows;
+  const double block = f64 ? 0.88 * 64.0 * nks + 820.0 : 1.07 * 32.0 * nks + 100.0;
+  const int group = wide(prec, nd) ? 8 : 16, agroup = wide(prec, nd) && tiles > kCUs ? 4 : group;
+  const double mine = (nblk + group - 1) / group * (group / 4) * block, rounds = (tiles + kCUs - 1) / kCUs;
+  double split = 0.0;
+  for (int S = 1; S <= 16 && S <= nblk; S *= 2) {
+    const int per = (nblk + S - 1) / S;
+    const double t = static_cast<double>((static_cast<long long>(tiles) * S + kCUs - 1) / kCUs) *
+                     ((per + agroup - 1) / agroup * (agroup / 4) * block + 1500.0);
+    if (S == 1 || t < split) split = t;
+  }
+  const double one = f64 ? rounds * (1.065 * mine + 11500.0 + 5.5 * p + (p > 128 ? 9100.0 : 0.0)) + 2500.0
+                         : rounds * (1.39 * mine + 4570.0 + 6.3 * p) + 13300.0;
+  const double rows = static_cast<double>(tiles) * p / kCUs;
+  const double apart = f64 ? 1.066 * split + 24100.0 + 68.0 * rows : 1.387 * split + 35500.0 + 12.2 * rows;
   return one <= apart;
 }
 

@@ -102,3 +102,37 @@ def test_fp32_one_launch_keeps_its_likelihoods():
     assert rel_err(kept, fresh).max() <= 1e-13      # same FP32 terms, FP64 sums in another order
     assert 0.0 < g.stats(2)["accept_rate"] < 1.0
     g.close()
+
+
+@pytest.mark.parametrize("prec,n,p,M", [("fp64", 90, 129, 4097), ("fp64", 130, 208, 4096), ("fp64", 50, 255, 4113),
+                                        ("fp32", 90, 257, 4097), ("fp32", 40, 400, 4128), ("fp32", 60, 511, 4096)])
+def test_wide_rows_beyond_one_block_per_cu(prec, n, p, M):
+    """Wide rows on both sides of 256 blocks of particles (8 and 4 waves per workgroup)."""
+    import torch
+    s, cfg, X, y, Xs = _sampler(n, p, prec)
+    b = particles(M, p, seed=n + p, scale=0.05)
+    bt = torch.from_numpy(b).to("cuda", torch.float64 if prec == "fp64" else torch.float32)
+    print(f"wide rows {prec} n={n} p={p} M={M}", flush=True)
+    rows = np.r_[0:40, M - 40:M]
+    ref = likelihood.loglik(bt.double().cpu().numpy()[rows], Xs, y)
+    ll = s.loglik(bt, prec).cpu().numpy()
+    assert rel_err(ll[rows], ref).max() <= (1e-10 if prec == "fp64" else 1e-4)
+    s.close()
+
+
+@pytest.mark.parametrize("prec,n,p,N", [("fp64", 2000, 200, 100), ("fp64", 100, 150, 4200), ("fp64", 3000, 100, 600),
+                                        ("fp32", 300, 129, 200), ("fp32", 120, 200, 4200), ("fp32", 6400, 100, 300)])
+def test_random_walk_apart_keeps_its_likelihoods(prec, n, p, N):
+    """Random walks on the side of separate launches: the kept log-likelihoods are those of the
+    particles (the same terms, FP64 sums in another order)."""
+    cfg, X, y, Xs = dataset("n2000_p50_rwm_fp32", n=n, p=p)
+    from paper_1106_0322_amd import SamplerConfig, SpaSMC
+    cfg = cfg.replace(n=n, p=p, N=N, T=3, sweeps=3, init_sweeps=4, lambdas=tuple(np.geomspace(2.0, 0.2, 3)))
+    print(f"random walk {prec} n={n} p={p} N={N}", flush=True)
+    g = SpaSMC(SamplerConfig.from_workload(cfg, prec=prec), X, y)
+    g.run()
+    beta, _ = g.particles()
+    kept, fresh = g.state_loglik().cpu().numpy(), g.loglik(beta, prec).cpu().numpy()
+    assert rel_err(kept, fresh).max() <= 1e-13
+    assert 0.0 < g.stats(2)["accept_rate"] < 1.0
+    g.close()
