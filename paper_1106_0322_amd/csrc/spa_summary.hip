@@ -215,9 +215,14 @@ __global__ __launch_bounds__(kColThreads) void sq_column_kernel(const VT *__rest
     else key[e] = key_of(vals[(size_t)i * p + j]);
     if constexpr (EPT > kColInline) q[e] = qin[i];
   }
+  // entries beyond M: no weight, and a key (of a NaN) that no level's prefix matches, or their
+  // additions of nothing to the last value's bucket would be most of a call of few values
 #pragma unroll
   for (int e = 0; e < EPT; ++e)
-    if (tid + kColThreads * e >= M) q[e] = 0;
+    if (tid + kColThreads * e >= M) {
+      key[e] = static_cast<KT>(~KT(0));
+      q[e] = 0;
+    }
   if (tid <= kSqMaxLevels) stot[tid] = 0ull;
   if constexpr (EPT <= kColInline) {
     double wv[EPT], mx = logw ? -INFINITY : 0.0;
@@ -273,13 +278,12 @@ __global__ __launch_bounds__(kColThreads) void sq_column_kernel(const VT *__rest
       }
     } else {
       // few values still match a level: one comparison per value and level, and the digit
-      // only for a wave that holds a match (threads beyond M repeat the last value with no weight:
-      // their additions of nothing to one bucket were most of a call at M = 1)
+      // only for a wave that holds a match
       for (int l = 0; l < lv.L; ++l) {
         const KT pre = static_cast<KT>(spre[l]);
 #pragma unroll
         for (int e = 0; e < EPT; ++e)
-          if ((key[e] >> hi) == pre && q[e] != 0) {
+          if ((key[e] >> hi) == pre) {
             const int b = static_cast<int>(key[e] >> lo) & ((1 << width) - 1);
             atomicAdd(&hist[l * kColStride + b + (b >> 5)], static_cast<unsigned long long>(q[e]));
           }
