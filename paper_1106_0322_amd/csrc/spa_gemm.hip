@@ -1,6 +1,6 @@
 // Log-likelihood contraction of all particles against the genotype matrix, on MFMA: BF16
-// hi+lo, and the FP32 gradient of many particles and of the FP32 MALA sweeps (the other FP32
-// and all FP64 evaluations are streamed, spa_stream.hip).
+// hi+lo, and every FP32 gradient, the FP32 MALA sweeps' included (FP32 log-likelihoods and all
+// FP64 evaluations are streamed, spa_stream.hip).
 //
 // For particles i and individuals k (Section 2 likelihood on standardised genotypes,
 // Section 3):
@@ -10,18 +10,18 @@
 //   g_ij   = (X_std^T y)_j - (sum_k sigma_ik X_kj - mu_j sum_k sigma_ik) / s_j,
 //            sigma_ik = logistic(eta_ik)   (the likelihood gradient X_std^T (y - sigma))
 //
-// Work decomposition.  A workgroup of 4 wave64s owns a tile of 64*PB particles; each wave
-// keeps the BF16 hi/lo (or FP32) fragments of its 16*PB particles in registers for
-// the whole pass.  Individuals are split into S contiguous ranges, one per workgroup of a
+// Work decomposition.  A workgroup of 8 wave64s (4 for rows of more than 256 markers) owns 16
+// particles per wave; each wave keeps the BF16 hi/lo (or FP32) fragments of its particles in
+// registers for the whole pass.  Individuals are split into S contiguous ranges, one per workgroup of a
 // "split"; the workgroup -> (split, particle tile) map follows the round-robin dispatch of
 // workgroups to the 8 XCDs so that the XCDs of one split share its genotype slice in their
-// L2.  A workgroup streams its slice in tiles of NT individuals through double-buffered
-// LDS (the next tile is prefetched into registers while the current one is used): the
-// individual-major tile feeds the forward MFMA (eta^T blocks, individuals x particles) and,
-// for the gradient, the marker-major tile feeds the adjoint MFMA G^T += X^T sigma^T, whose
-// B operand is the logistic of the forward output taken straight from the accumulator
-// registers (a lane of an eta^T block holds four individuals of one particle, i.e. the K
-// slots of an MFMA B fragment).  Softplus sums: per lane and tile, sum max(eta, 0) plus
+// L2.  A workgroup streams its slice in tiles of NT individuals through double-buffered LDS (the
+// next tile is copied there while the current one is used; FP8 codes are widened to BF16 on the
+// way, through registers): the individual-major tile feeds the forward MFMA (eta^T blocks,
+// individuals x particles) and, for the gradient, the marker-major tile feeds the adjoint MFMA
+// G^T += X^T sigma^T, whose B operand is the logistic of the forward output taken straight from
+// the accumulator registers (a lane of an eta^T block holds four individuals of one particle,
+// i.e. the K slots of an MFMA B fragment).  Softplus sums: per lane and tile, sum max(eta, 0) plus
 // one log of prod (1 + exp(-|eta|)) (the product of at most 16 factors in (1, 2] cannot
 // overflow), accumulated across tiles in FP64 in a fixed order; in reduced precision
 // sum max(eta, 0) is taken as half of sum |eta| (the standardised genotypes are centred,

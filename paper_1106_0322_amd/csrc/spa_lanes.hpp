@@ -78,9 +78,9 @@ __device__ __forceinline__ float wave_total_f32(float v) {
 // r C + (c ^ row_swizzle<C>(r)).  A 16-byte read of a wave is served in four parts of 16 lanes, of
 // two neighbouring lane groups g and g ^ 1: rows 0..3 and 12..15 of one, 4..11 of the other.  The
 // numbers here put chunk g of the former and g ^ 1 of the latter at the 16 positions of a line of
-// the 64 banks, once each (checked by the bank-conflict counter).  Rows padded to an odd stride,
-// the form before, do so for 16 rows of one lane group only: every fragment read took 8 cycles
-// for 4.
+// the 64 banks, once each (checked by the bank-conflict counter).  Rows padded to an odd stride
+// do so for 16 rows of one lane group only: every fragment read takes 8 cycles for 4.  (FP32
+// fragments are read word by word; their tiles are padded at some widths, spa_gemm.hip.)
 // (With it and with fragments read further ahead: a MALA scale of 16384 particles, n = 5000, BF16,
 // p = 200 1660 -> 1615 us, p = 250 2142 -> 1848; log-likelihoods of 16384 particles, n = 10000,
 // p = 500, 361 -> 315 us; four FP8 terms, n = 5000, p = 200, 86 -> 79 us.)
