@@ -166,7 +166,7 @@ spa_status spa_smc_loglik(spa_smc *h, const void *beta_dev, int32_t M, int32_t b
  * Errors: as spa_smc_loglik; SPA_ERR_ARG also for the FP8 multi-term precisions and for
  * an M whose buffers exceed the array (the message gives the bytes needed);
  * SPA_ERR_STATE if the genotype copy of prec has not been prepared (the handle's own
- * precision always is; another one after one spa_smc_loglik call with it).
+ * precision always is; another one after one spa_smc_loglik or spa_smc_grad call with it).
  */
 spa_status spa_smc_loglik_noalloc(spa_smc *h, const void *beta_dev, int32_t M, int32_t beta_is_fp64,
                                   spa_prec prec, double *loglik_dev);

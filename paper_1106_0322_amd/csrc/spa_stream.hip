@@ -17,15 +17,15 @@
 // What bounds it: the FP32/FP64 matrix rate at large M (K padded to the next multiple of 4
 // only), the elementwise FP64 exp and log for short FP64 rows, launch latency at small M.
 // Measured per call, tiled kernel with its packing launch before -> streamed (us): FP32
-// loglik n = 1859, p = 184, M = 1000: 51 -> 18; n = 5000, p = 200, M = 16384: 348 -> 297;
-// n = 10000, p = 500, M = 16: 245 -> 35; FP64 loglik n = 500, p = 10, M = 64: 15.2 -> 7.4;
-// n = 10000, p = 30, M = 30: 123 -> 22; n = 5000, p = 200, M = 16384: 1056 -> 765; FP64
-// gradient n = 10000, p = 250, M = 300: 524 -> 156; n = 5000, p = 200, M = 16384: 1996 -> 1763.
+// loglik n = 1859, p = 184, M = 1000: 51 -> 15; n = 5000, p = 200, M = 16384: 351 -> 295;
+// n = 10000, p = 500, M = 16: 245 -> 18; FP64 loglik n = 500, p = 10, M = 64: 15.3 -> 7.4;
+// n = 10000, p = 30, M = 30: 123 -> 10; n = 5000, p = 200, M = 16384: 1060 -> 777; FP64
+// gradient n = 10000, p = 250, M = 300: 517 -> 132; n = 5000, p = 200, M = 16384: 1980 -> 1672.
 //
 // Sums: FP32 takes log2(prod (1 + e)) and half of sum |z| per lane and block (as the BF16
 // contraction does: the genotypes are centred); FP64 takes sum max(eta, 0) and one log1p
-// of the product of the lane's four factors 1 + e^-|eta|, less one, per block; both add per block in FP64,
-// then lane groups, waves and ranges in order.
+// of the product of the lane's four factors 1 + e^-|eta|, less one, per block; both add per block in
+// FP64, then lane groups, waves and ranges in order.
 #include <algorithm>
 #include <cmath>
 
@@ -227,8 +227,8 @@ __device__ __forceinline__ void stream_blocks(const uint32_t *__restrict__ Xb, c
 }
 
 // Particle blocks from which each wave of a gradient workgroup takes its own: then every
-// SIMD has one (n = 200, p = 200, M = 30000 FP64: 361 us per call with shared blocks, the
-// tiled kernel's 275).
+// SIMD has one (n = 200, p = 200, M = 30000 FP64: 223 us per call, 361 with shared blocks; tiled
+// kernel before 251).
 constexpr int kOwnTiles = 1024;
 
 // Waves per workgroup of the contraction: the gradient's accumulators leave one wave per
@@ -239,7 +239,7 @@ constexpr int stream_waves() { return GRAD ? 4 : 8; }
 // Rows of which a workgroup of 8 waves fills a CU's registers.  With more blocks of particles than
 // CUs they run in workgroups of 4, two to a CU, one of which packs its rows while the other
 // contracts: log-likelihoods M = 32768, FP64 n = 130, p = 250 109 us in 8 waves, 82 in 4 (tiled kernel
-// before 103), FP32 n = 300, p = 500 165 and 140; with one block per CU 8 waves are up to 28 % faster.
+// before 103), FP32 n = 300, p = 500 165 and 127; with one block per CU 8 waves are up to 28 % faster.
 constexpr bool wide(Prec prec, int nd) { return nd > (prec == Prec::F64 ? 8 : 16); }
 constexpr int kCUs = 256;
 
@@ -433,9 +433,9 @@ __global__ void stream_final_ll_kernel(const double *__restrict__ part, const do
   ll[i] = yb[i] - sp;
 }
 
-// Gradient rows, LP lanes per particle and U coefficients per lane at a time: the ranges' adjoints summed in order, the
-// standardisation, the prior's gradient and log density (the log of a product of U
-// factors where that product is finite), each in FP64 and rounded once to the output type.
+// Gradient rows, LP lanes per particle and U coefficients per lane at a time: the ranges' adjoints
+// summed in order, the standardisation, the prior's gradient and log density (the log of a product
+// of U factors where that product is finite), each in FP64 and rounded once to the output type.
 // Bound by memory: S float or double adjoints, the particle and the gradient of a coefficient.
 // For the tiled contractions it replaces a finalize, a prior and (FP64 callers) a conversion
 // launch, 45 us at 16384 x 200, BF16, by one of 35 us.
@@ -510,8 +510,9 @@ __global__ __launch_bounds__(256) void stream_final_grad_kernel(const double *__
 // Philox block or Box-Muller pair per thread, shortened the FP32 sweep by 2 % and lengthened
 // the FP64 one by 6 %: the row work is a latency chain, not a throughput one.)
 // FP32 rows leave room for two workgroups of 8 waves per CU (128 VGPRs), whose row work and
-// contractions overlap (n = 5000, p = 200, N = 16384: 3.71 -> 3.56 ms per scale of 10 sweeps,
-// one workgroup against two); FP64 rows would spill (663 -> 792 us at n = 1000, p = 100).
+// contractions overlap (rows of 200 markers, which have since left this form: n = 5000, N = 16384
+// 3.71 -> 3.56 ms per scale of 10 sweeps, one workgroup against two); FP64 rows would spill
+// (663 -> 792 us at n = 1000, p = 100).
 template <Prec P, int ND, int NW>
 __global__ __launch_bounds__(64 * NW, P == Prec::F32 ? 4 : 2) void rwm_sweeps_kernel(RwmArgs a) {
   using T = ST<P>;

@@ -97,15 +97,16 @@ __device__ __forceinline__ uint64_t wave_scan_u64(uint64_t v) {
 // weights of particles t, t + 1024, ... (EPT of them) in registers.  Up to kColInline of
 // them every workgroup also quantises the weights itself, which saves a launch; above, the
 // M correctly rounded divisions in every workgroup cost more (about 20 us at M = 32768)
-// than the one launch that does them once.  Then the total, the concentrations' sums, and one radix pass per 11-bit digit: a histogram per level in LDS and, per level,
-// one wave that scans its 2048 buckets (rows of 32 buckets padded by one, so that a lane's
-// 32 consecutive buckets are read without bank conflicts).  In the first pass every level
-// still matches every value, so one histogram serves all of them.
+// than the one launch that does them once.  Then the total, the concentrations' sums, and one radix
+// pass per 11-bit digit: a histogram per level in LDS and, per level, one wave that scans its 2048
+// buckets (rows of 32 buckets padded by one, so that a lane's 32 consecutive buckets are read
+// without bank conflicts).  In the first pass every level still matches every value, so one
+// histogram serves all of them.
 // Bound: the latency of the passes (about 2.5 us per digit, LDS atomics and barriers) and,
 // for long rows, the transposed copy.  Measured per call at M = 16384, p = 200 FP32, 3
 // levels and 2 tolerances, quantisation + column kernel: 12.7 + 21.7 us, against 190 us of
-// kernels for the multi-pass form (call 216 -> 57 us); M = 1024, p = 200: call 89 -> 29 us;
-// M = 16384, p = 400 FP64: 388 -> 102 us.  Sets above the register limit gain nothing from
+// kernels for the multi-pass form (call 223 -> 53 us); M = 1024, p = 200: call 83 -> 35 us;
+// M = 16384, p = 400 FP64: 397 -> 107 us.  Sets above the register limit gain nothing from
 // a second value buffer in LDS, which the histograms fill, and stay with the multi-pass form.
 constexpr int kColThreads = 1024;
 constexpr int kColWaves = kColThreads / 64;
