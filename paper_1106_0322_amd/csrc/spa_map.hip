@@ -277,8 +277,9 @@ __global__ __launch_bounds__(NT) void map_em_kernel(MapArgs a, int resident) {
   };
   // a coefficient moves by delta (the same in every lane); xc: its column's code_values
   auto move = [&](const double delta, const double xc, const uint32_t (&wd)[WN]) {
-    // SELECT: the factors broadcast in each four lanes and selected (padded individuals: any of them, E is infinite); n = 1000, p = 100, every
-    // coefficient non-zero, 0.82 -> 0.73 us per update.  Else lanes 0..3 put them in the wave's
+    // SELECT: the factors broadcast in each four lanes and selected (padded individuals: any of
+    // them, E is infinite); n = 1000, p = 100, every coefficient non-zero, 0.82 -> 0.73 us per
+    // update.  Else lanes 0..3 put them in the wave's
     // table (1 for code 3; n = 2000: 1.00 us, selected 1.08); a wave's LDS accesses are processed in
     // order, and the wave barrier keeps the compiler from moving the table reads above the write
     double f0 = 0.0, f1 = 0.0, f2 = 0.0;
